@@ -1323,36 +1323,6 @@ __global__ void avgpool_bwd_kernel(const float* df, int N, int HW, int C, T* dx)
 }
 
 // ------------------------------------------------------------- classifier
-// One block per row: each thread takes a strided slice of the features for 8
-// classes at a time, then a fixed-order wave and block reduction.
-__global__ __launch_bounds__(256) void fc_fwd_kernel(const float* f, const float* W, const float* b,
-                                                     int N, int I, int J, float* z) {
-  __shared__ float red[4][8];
-  const int n = blockIdx.x, t = threadIdx.x, lane = t & 63, wave = t >> 6;
-  const float* fr = f + (long long)n * I;
-  for (int j0 = 0; j0 < J; j0 += 8) {
-    float s[8];
-#pragma unroll
-    for (int k = 0; k < 8; ++k) s[k] = 0.f;
-    for (int i = t; i < I; i += 256) {
-      const float x = fr[i];
-#pragma unroll
-      for (int k = 0; k < 8; ++k)
-        if (j0 + k < J) s[k] += x * W[(long long)(j0 + k) * I + i];
-    }
-#pragma unroll
-    for (int k = 0; k < 8; ++k) {
-      float v = s[k];
-      for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-      if (lane == 0) red[wave][k] = v;
-    }
-    __syncthreads();
-    if (t < 8 && j0 + t < J)
-      z[(long long)n * J + j0 + t] = ((red[0][t] + red[1][t]) + (red[2][t] + red[3][t])) + b[j0 + t];
-    __syncthreads();
-  }
-}
-
 __global__ __launch_bounds__(256) void softmax_ce_kernel(const float* z, const int32_t* labels,
                                                          const int32_t* idx, int N, int J,
                                                          float* dz, float* out) {
@@ -1404,35 +1374,11 @@ __global__ __launch_bounds__(256) void softmax_ce_kernel(const float* z, const i
   }
 }
 
-__global__ void fc_bwd_w_kernel(const float* dz, const float* f, int N, int I, int J, float* dW,
-                                float* db) {
-  const int t = blockIdx.x * blockDim.x + threadIdx.x;
-  if (t < J * I) {
-    const int j = t / I, i = t % I;
-    float s = 0.f;
-    for (int n = 0; n < N; ++n) s += dz[(long long)n * J + j] * f[(long long)n * I + i];
-    dW[t] = s;
-  }
-  if (t < J) {
-    float s = 0.f;
-    for (int n = 0; n < N; ++n) s += dz[(long long)n * J + t];
-    db[t] = s;
-  }
-}
-
-__global__ void fc_bwd_x_kernel(const float* dz, const float* W, int N, int I, int J, float* df) {
-  const long long t = blockIdx.x * (long long)blockDim.x + threadIdx.x;
-  if (t >= (long long)N * I) return;
-  const int n = (int)(t / I), i = (int)(t % I);
-  float s = 0.f;
-  for (int j = 0; j < J; ++j) s += dz[(long long)n * J + j] * W[(long long)j * I + i];
-  df[t] = s;
-}
-
 // ----------------------------------------------------- fused classifier head
 // Forward: one block per sample: pooled[n][c] = mean over the HW pixels of
-// x[n] (or the given features f when x is null), then the logits as in
-// fc_fwd_kernel.  Backward: one launch for softmax cross-entropy, the
+// x[n] (or the given features f when x is null), then the logits (a
+// strided slice of the features per thread, a fixed-order wave and block
+// reduction; none with J = 0).  Backward: one launch for softmax cross-entropy, the
 // classifier's weight and bias gradients and the average-pool backward.
 // Every block recomputes the (6-wide) softmax rows it needs from the logits,
 // so no intermediate dz array or extra launch is needed.
@@ -2377,28 +2323,10 @@ hipError_t avgpool_bwd(int dt, const float* df, int N, int HW, int C, void* dx,
   });
 }
 
-hipError_t fc_fwd(const float* f, const float* W, const float* b, int N, int I, int J, float* z,
-                  hipStream_t stream) {
-  if (N == 0) return hipSuccess;
-  hipLaunchKernelGGL(fc_fwd_kernel, dim3(N), dim3(256), 0, stream, f, W, b, N, I, J, z);
-  return hipGetLastError();
-}
-
 hipError_t softmax_ce(const float* z, const int32_t* labels, const int32_t* idx, int N, int J,
                       float* dz, float* out, hipStream_t stream) {
   hipLaunchKernelGGL(softmax_ce_kernel, dim3(1), dim3(256), 0, stream, z, labels, idx, N, J, dz,
                      out);
-  return hipGetLastError();
-}
-
-hipError_t fc_bwd(const float* dz, const float* f, const float* W, int N, int I, int J, float* dW,
-                  float* db, float* df, hipStream_t stream) {
-  hipLaunchKernelGGL(fc_bwd_w_kernel, dim3(cdiv(J * I, 256)), dim3(256), 0, stream, dz, f, N, I, J,
-                     dW, db);
-  if (df) {
-    hipLaunchKernelGGL(fc_bwd_x_kernel, dim3(grid_for((long long)N * I)), dim3(256), 0, stream, dz,
-                       W, N, I, J, df);
-  }
   return hipGetLastError();
 }
 
@@ -2606,18 +2534,6 @@ hipError_t permute_weights(const float* src, float* dst, const long long* tab, i
                            long long total, int to_internal, hipStream_t stream) {
   hipLaunchKernelGGL(permute_kernel, dim3(grid_for(total)), dim3(256), 0, stream, src, dst, tab, n,
                      total, to_internal);
-  return hipGetLastError();
-}
-
-__global__ void relu_f32_kernel(float* y, const float* x, const float* mask, long long n) {
-  for (long long i = blockIdx.x * (long long)blockDim.x + threadIdx.x; i < n;
-       i += (long long)gridDim.x * blockDim.x)
-    y[i] = mask ? (mask[i] > 0.f ? x[i] : 0.f) : fmaxf(x[i], 0.f);
-}
-
-hipError_t relu_f32(float* y, const float* x, const float* mask, long long n, hipStream_t stream) {
-  if (n <= 0) return hipSuccess;
-  hipLaunchKernelGGL(relu_f32_kernel, dim3(grid_for(n)), dim3(256), 0, stream, y, x, mask, n);
   return hipGetLastError();
 }
 

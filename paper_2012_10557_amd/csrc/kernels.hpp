@@ -247,20 +247,22 @@ hipError_t avgpool_bwd(int dt, const float* df, int N, int HW, int C, void* dx,
                        hipStream_t stream);
 
 // --------------------------------------------------------------- classifier
-// z[N, J] = f[N, I] W[J, I]^T + b
+// z[N, J] = f[N, I] W[J, I]^T + b, then max(., 0) if relu
 hipError_t fc_fwd(const float* f, const float* Wt, const float* b, int N, int I, int J, float* z,
-                  hipStream_t stream);
+                  hipStream_t stream, bool relu = false);
 // Softmax cross-entropy over rows of z[N, J] with labels (selected through
 // `idx` when non-null): dz = (softmax - onehot)/N, out[0] = mean loss,
 // out[1] = correct count (as float), out[2] = non-finite flag.
 hipError_t softmax_ce(const float* z, const int32_t* labels, const int32_t* idx, int N, int J,
                       float* dz, float* out, hipStream_t stream);
-// dW[J, I] = dz^T f, db = column sums of dz, df = dz W (df may be null).
+// dW[J, I] = dz^T f, db = column sums of dz, df = dz W (df may be null); with
+// mask [N, I], df is zero where mask is not positive (backward through a ReLU
+// whose output is mask).
 hipError_t fc_bwd(const float* dz, const float* f, const float* Wt, int N, int I, int J, float* dW,
-                  float* db, float* df, hipStream_t stream);
+                  float* db, float* df, hipStream_t stream, const float* mask = nullptr);
 // Fused classifier head.  Forward: pooled[N, I] (fp32) = mean over HW pixels
 // of x[N, HW, I] (x null: features f are used and pooled is not written),
-// z = pooled W^T + b.  Backward (J <= 16, I <= 512; head_backward_fused):
+// z = pooled W^T + b (J = 0: the pooled features only).  Backward (J <= 16, I <= 512; head_backward_fused):
 // softmax cross-entropy of z with labels (through idx when non-null) as in
 // softmax_ce (out[0..2]), dW = dz^T f, db = column sums of dz and, when dout
 // is non-null, dout[N, HW, I] = (dz W) / HW.
@@ -287,9 +289,6 @@ hipError_t head_backward(int dt, const float* z, const int32_t* labels, const in
 hipError_t count_correct(const float* z, const int32_t* labels, int N, int J, int32_t* count,
                          hipStream_t stream);
 hipError_t argmax_rows(const float* z, int N, int J, int32_t* out, hipStream_t stream);
-// y = max(x, 0) (mask null) or y = x where mask > 0, else 0 (the ReLU
-// backward through the ReLU's output), over n fp32 values; y may be x.
-hipError_t relu_f32(float* y, const float* x, const float* mask, long long n, hipStream_t stream);
 
 // -------------------------------------------------------------- optimiser
 // v = mu v + g; w = w - lr v over n floats.

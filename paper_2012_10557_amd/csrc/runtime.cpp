@@ -427,8 +427,7 @@ static hipError_t eval_forward(const Net& net, const Geo& g, const void* shadow,
     } else {  // s == 5
       const float* f = reinterpret_cast<const float*>(cur);
       if (net.hidden > 0) {
-        EKYA_HIP(fc_fwd(f, master + net.fc1_w, master + net.fc1_b, n, 512, net.hidden, b.hid, st));
-        EKYA_HIP(relu_f32(b.hid, b.hid, nullptr, (long long)n * net.hidden, st));
+        EKYA_HIP(fc_fwd(f, master + net.fc1_w, master + net.fc1_b, n, 512, net.hidden, b.hid, st, true));
         f = b.hid;
       }
       EKYA_HIP(fc_fwd(f, master + net.fc_w, master + net.fc_b, n, net.head_in(), net.n_classes,
@@ -673,9 +672,12 @@ static hipError_t train_head_forward(TrainJob& j, int nb, const void* x) {
   if (net.hidden == 0)
     return head_forward(j.dt, x, hw, f, j.master + net.fc_w, j.master + net.fc_b, nb, 512,
                         net.n_classes, pooled, j.logits, j.st);
-  EKYA_HIP(head_forward(j.dt, x, hw, f, j.master + net.fc1_w, j.master + net.fc1_b, nb, 512,
-                        net.hidden, pooled, j.hid, j.st));
-  EKYA_HIP(relu_f32(j.hid, j.hid, nullptr, (long long)nb * net.hidden, j.st));
+  if (x) {
+    EKYA_HIP(head_forward(j.dt, x, hw, nullptr, nullptr, nullptr, nb, 512, 0, pooled, nullptr, j.st));
+    f = pooled;
+  }
+  EKYA_HIP(fc_fwd(f, j.master + net.fc1_w, j.master + net.fc1_b, nb, 512, net.hidden, j.hid, j.st,
+                  true));
   return fc_fwd(j.hid, j.master + net.fc_w, j.master + net.fc_b, nb, net.hidden, net.n_classes,
                 j.logits, j.st);
 }
@@ -793,8 +795,7 @@ static hipError_t train_backward(TrainJob& j, int nb, const int32_t* fid, float*
     // hidden layer, then the average-pool backward
     EKYA_HIP(softmax_ce(j.logits, j.labels, fid, nb, net.n_classes, j.dz, ce, st));
     EKYA_HIP(fc_bwd(j.dz, j.hid, j.master + net.fc_w, nb, net.hidden, net.n_classes,
-                    j.grad + net.fc_w, j.grad + net.fc_b, j.dhid, st));
-    EKYA_HIP(relu_f32(j.dhid, j.dhid, j.hid, (long long)nb * net.hidden, st));
+                    j.grad + net.fc_w, j.grad + net.fc_b, j.dhid, st, j.hid));
     EKYA_HIP(fc_bwd(j.dhid, f, j.master + net.fc1_w, nb, 512, net.hidden, j.grad + net.fc1_w,
                     j.grad + net.fc1_b, j.lowest == 5 ? nullptr : j.dpooled, st));
     if (j.lowest < 5) EKYA_HIP(avgpool_bwd(dt, j.dpooled, nb, hw, 512, dout, st));
