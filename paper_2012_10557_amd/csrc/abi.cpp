@@ -321,22 +321,30 @@ bool chan_ok(int dt, int C, bool allow3) {
   return C > 0 && C % ekya::dtype_vec(dt) == 0;
 }
 
-// Repack fp32 [K][C][R][S] weights into the kernels' low-precision layouts.
-hipError_t pack_one(int dt, const float* w, int K, int C, int R, int S, int Cp, Tmp& tmp,
-                    void** krsc, void** crsk, hipStream_t st) {
-  const long long n = (long long)K * C * R * S;
-  float* m = tmp.get<float>(n);
-  long long* tab = tmp.get<long long>(16);
+// fp32 [K][C][R][S] weights in one of the kernels' low-precision layouts:
+// [K][RS][Cp] (crsk false) or [C][RS][K].
+hipError_t pack_one(int dt, const float* w, int K, int C, int R, int S, int Cp, bool crsk, Tmp& tmp,
+                    void** out, hipStream_t st) {
+  const long long RS = (long long)R * S;
   const size_t es = ekya::dtype_size(dt);
-  char* sh = tmp.get<char>((size_t)(K * R * S * Cp + n) * es);
-  if (!m || !tab || !sh) return hipErrorOutOfMemory;
-  long long h[13] = {0, K, C, R, S, 0, K, R, S, C, Cp, 0, (long long)K * R * S * Cp};
+  const long long n = K * RS * Cp;
+  const bool both = crsk && !ekya::pack_crsk_ok((int)RS);  // through the [K][RS][C] layouts
+  long long* tab = tmp.get<long long>(16);
+  char* sh = tmp.get<char>((both ? 2 : 1) * n * es);
+  float* m = both ? tmp.get<float>(n) : nullptr;
+  if (!tab || !sh || (both && !m)) return hipErrorOutOfMemory;
+  *out = sh;
+  if (both) {
+    const long long h[15] = {0, K, C, RS, Cp, -1, -1, 0, K, R, S, C, Cp, 0, n};
+    *out = sh + n * es;
+    EKYA_HIP(hipMemcpy(tab, h, sizeof(h), hipMemcpyHostToDevice));
+    EKYA_HIP(ekya::weights_to_internal(dt, w, m, m, tab, 1, (int)RS, nullptr, st));
+    return ekya::pack_conv_weights(dt, m, tab + 7, 1, sh, st);
+  }
+  const long long h[7] = {0, K, C, RS, Cp, crsk ? -1 : 0, crsk ? 0 : -1};
   EKYA_HIP(hipMemcpy(tab, h, sizeof(h), hipMemcpyHostToDevice));
-  EKYA_HIP(ekya::permute_weights(w, m, tab, 1, n, 1, st));
-  EKYA_HIP(ekya::pack_conv_weights(dt, m, tab + 5, 1, sh, st));
-  *krsc = sh;
-  *crsk = sh + (size_t)K * R * S * Cp * es;
-  return hipSuccess;
+  if (crsk) return ekya::pack_crsk(dt, w, tab, 1, sh, st);
+  return ekya::weights_to_internal(dt, w, nullptr, nullptr, tab, 1, (int)RS, sh, st);
 }
 
 hipError_t pad_input(int dt, const void* x, int N, int H, int W, int C, int& Cp, Tmp& tmp,
@@ -389,9 +397,9 @@ ekya_status ekya_op_conv2d(int precision, const void* x, int N, int H, int W, in
   Tmp tmp;
   int Cp;
   const void* xp;
-  void *krsc, *crsk;
+  void* krsc;
   hipError_t e = pad_input(precision, x, N, H, W, C, Cp, tmp, &xp, st);
-  if (e == hipSuccess) e = pack_one(precision, w, K, C, R, S, Cp, tmp, &krsc, &crsk, st);
+  if (e == hipSuccess) e = pack_one(precision, w, K, C, R, S, Cp, false, tmp, &krsc, st);
   const ekya::ConvGeom g = make_geom(N, H, W, Cp, K, R, S, stride, pad);
   const size_t wsf = ekya::conv_split_workspace_floats(precision, g, false);
   float* ws = wsf ? tmp.get<float>(wsf) : nullptr;
@@ -408,8 +416,8 @@ ekya_status ekya_op_conv2d_dgrad(int precision, const void* dy, const float* w, 
     return fail(nullptr, EKYA_ERR_INVALID_ARG, "invalid conv2d_dgrad arguments");
   hipStream_t st = (hipStream_t)stream;
   Tmp tmp;
-  void *krsc, *crsk;
-  hipError_t e = pack_one(precision, w, K, C, R, S, C, tmp, &krsc, &crsk, st);
+  void* crsk;
+  hipError_t e = pack_one(precision, w, K, C, R, S, C, true, tmp, &crsk, st);
   const ekya::ConvGeom g = make_geom(N, H, W, C, K, R, S, stride, pad);
   const size_t wsf = ekya::conv_split_workspace_floats(precision, g, true);
   float* ws = wsf ? tmp.get<float>(wsf) : nullptr;
@@ -436,10 +444,10 @@ ekya_status ekya_op_conv2d_wgrad(int precision, const void* x, const void* dy, i
   if (!part || !krsc || !tab) e = hipErrorOutOfMemory;
   if (e == hipSuccess) e = ekya::conv_wgrad(precision, g, xp, dy, part, krsc, C, st);
   if (e == hipSuccess) {
-    long long h[5] = {0, K, C, R, S};
+    long long h[7] = {0, K, C, (long long)R * S, C, -1, -1};
     e = hipMemcpy(tab, h, sizeof(h), hipMemcpyHostToDevice);
   }
-  if (e == hipSuccess) e = ekya::permute_weights(krsc, dw, tab, 1, (long long)K * C * R * S, 0, st);
+  if (e == hipSuccess) e = ekya::weights_to_canonical(krsc, dw, tab, 1, R * S, st);
   return sync_status(st, e);
 }
 

@@ -1970,37 +1970,6 @@ __global__ void sgd_ranges_kernel(float* w, float* v, const float* g, const long
   }
 }
 
-// tab row: off, K, C, R, S
-__global__ void permute_kernel(const float* src, float* dst, const long long* tab, int ntab,
-                               long long total, int to_internal) {
-  for (long long i = blockIdx.x * (long long)blockDim.x + threadIdx.x; i < total;
-       i += (long long)gridDim.x * blockDim.x) {
-    int lo = 0, hi = ntab - 1;  // last row with off <= i
-    while (lo < hi) {
-      int mid = (lo + hi + 1) >> 1;
-      if (tab[5 * mid] <= i) lo = mid; else hi = mid - 1;
-    }
-    const long long* t = tab + 5 * lo;
-    const long long off = t[0], l = i - off;
-    const int C = (int)t[2], R = (int)t[3], S = (int)t[4];
-    if (R * S * C == 1 || (R == 1 && S == 1)) {  // no reordering needed
-      dst[i] = src[i];
-      continue;
-    }
-    if (to_internal) {
-      // l indexes [K][C][R][S]; destination [K][R][S][C]
-      const int s = (int)(l % S), r = (int)((l / S) % R), c = (int)((l / ((long long)S * R)) % C);
-      const long long k = l / ((long long)S * R * C);
-      dst[off + ((k * R + r) * S + s) * C + c] = src[i];
-    } else {
-      // l indexes [K][R][S][C]; destination [K][C][R][S]
-      const int c = (int)(l % C), s = (int)((l / C) % S), r = (int)((l / ((long long)C * S)) % R);
-      const long long k = l / ((long long)C * S * R);
-      dst[off + ((k * C + c) * R + r) * S + s] = src[i];
-    }
-  }
-}
-
 template <typename F>
 hipError_t by_type(int dt, F&& f) {
   if (dt == DT_F32) f((float*)nullptr); else f((bf16*)nullptr);
@@ -2527,13 +2496,6 @@ hipError_t sgd_momentum_ranges(float* w, float* v, const float* g, const long lo
   if (n == 0 || max_len == 0) return hipSuccess;
   hipLaunchKernelGGL(sgd_ranges_kernel, dim3(grid_for(max_len, 256, 1024), n), dim3(256), 0, stream,
                      w, v, g, tab, lr, mu);
-  return hipGetLastError();
-}
-
-hipError_t permute_weights(const float* src, float* dst, const long long* tab, int n,
-                           long long total, int to_internal, hipStream_t stream) {
-  hipLaunchKernelGGL(permute_kernel, dim3(grid_for(total)), dim3(256), 0, stream, src, dst, tab, n,
-                     total, to_internal);
   return hipGetLastError();
 }
 

@@ -332,10 +332,24 @@ hipError_t cast_from_f32(int dt, const float* src, long long n, void* dst, hipSt
 // K, R, S, C0, Cp, krsc_off (elements of dt), crsk_off (elements, -1 = skip).
 hipError_t pack_conv_weights(int dt, const float* master, const long long* tab, int n,
                              void* shadow, hipStream_t stream);
-// Table row per tensor: off, K, C, R, S (conv) or off, n, 0, 0, 0 (other):
-// to_internal = 1 permutes [K][C][R][S] -> [K][R][S][C], 0 the inverse.
-hipError_t permute_weights(const float* src, float* dst, const long long* tab, int n,
-                           long long total, int to_internal, hipStream_t stream);
+// Between the canonical layout (convolutions [K][C][RS]) and the internal one
+// ([K][RS][C]).  Table row per tensor: off, K, C, RS, Cp, krsc_off, crsk_off
+// (offsets of its low-precision copies in elements of dt, -1: none), or off,
+// n, 1, 1, 1, -1, -1 for anything but a convolution.  max_taps: the largest
+// RS of the table.  weights_to_internal writes `master` (null: none) for the
+// rows with a krsc copy, `rest` (the same array, or with master null where
+// the others go) for those without, and with `shadow` the [K][RS][Cp]
+// copies in the same pass.
+hipError_t weights_to_internal(int dt, const float* canonical, float* master, float* rest,
+                               const long long* tab, int n, int max_taps, void* shadow,
+                               hipStream_t stream);
+hipError_t weights_to_canonical(const float* master, float* canonical, const long long* tab, int n,
+                                int max_taps, hipStream_t stream);
+// The [C][RS][K] copies of the rows that have one, from the canonical array
+// (pack_crsk_ok: filters it takes).
+bool pack_crsk_ok(int taps);
+hipError_t pack_crsk(int dt, const float* canonical, const long long* tab, int n, void* shadow,
+                     hipStream_t stream);
 
 // ------------------------------------------------------------- diagnostics
 // n one-wavefront workgroups; workgroup i writes the compute unit it ran on,

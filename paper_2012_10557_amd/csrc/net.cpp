@@ -86,20 +86,22 @@ Net Net::build(int n_classes, int dt, int hidden) {
   return n;
 }
 
-std::vector<long long> Net::permute_table() const {
-  // rows (off, K, C, R, S), sorted by offset; non-conv segments use (off, n, 1, 1, 1)
+std::vector<long long> Net::layout_table() const {
+  // BatchNorm vectors between two convolutions are one row, as are the last
+  // stage's, and the classifier: rows never straddle a stage
   std::vector<long long> t;
   long long cur = 0;
-  size_t bi = 0;
+  auto plain = [&](long long end) {
+    if (end > cur) t.insert(t.end(), {cur, end - cur, 1, 1, 1, -1, -1});
+    cur = end;
+  };
   for (const ConvL& c : conv) {
-    if (c.off > cur) {  // BatchNorm vectors before this conv
-      t.insert(t.end(), {cur, c.off - cur, 1, 1, 1});
-    }
-    t.insert(t.end(), {c.off, c.cout, c.cin, c.R, c.S});
+    plain(c.off);
+    t.insert(t.end(), {c.off, c.cout, c.cin, (long long)c.R * c.S, c.cin_pad, c.sh_krsc, c.sh_crsk});
     cur = c.off + (long long)c.cout * c.cin * c.R * c.S;
   }
-  (void)bi;
-  if (total > cur) t.insert(t.end(), {cur, total - cur, 1, 1, 1});
+  plain(stage_begin[5]);
+  plain(total);
   return t;
 }
 

@@ -59,7 +59,7 @@ struct Net {
   int head_in() const { return hidden > 0 ? hidden : 512; }
 
   // Host tables for the kernels (see kernels.hpp for row formats).
-  std::vector<long long> permute_table() const;              // every tensor
+  std::vector<long long> layout_table() const;  // every tensor, in order of offset
   std::vector<long long> fold_table(int lo_stage, int hi_stage) const;  // BNs of stages
   std::vector<long long> pack_table(int lo_stage, int hi_stage, bool with_crsk) const;
 };

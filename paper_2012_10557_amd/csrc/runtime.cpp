@@ -78,6 +78,9 @@ static std::vector<long long> sgd_rest_table(const Net& net, int lo, long long* 
 }
 
 // ----------------------------------------------------------------- tables
+constexpr int kLayoutCols = 7;
+constexpr int kMaxTaps = 49;  // the stem's 7 x 7 filter
+
 static hipError_t upload_tables(const Net& net, Tables& t) {
   std::vector<long long> all;
   std::vector<std::pair<const long long**, size_t>> fix;
@@ -86,13 +89,16 @@ static hipError_t upload_tables(const Net& net, Tables& t) {
     *n = (int)(v.size() / row);
     all.insert(all.end(), v.begin(), v.end());
   };
-  put(net.permute_table(), &t.permute, &t.n_permute, 5);
+  const std::vector<long long> layout = net.layout_table();
+  put(layout, &t.layout, &t.n_layout, kLayoutCols);
   put(net.fold_table(0, 5), &t.fold_all, &t.n_fold_all, 6);
   put(net.pack_table(0, 4, false), &t.pack_all, &t.n_pack_all, 8);
   for (int lo = 0; lo <= 5; ++lo) {
     put(net.fold_table(lo, 5), &t.fold_train[lo], &t.n_fold_train[lo], 6);
-    put(net.pack_table(0, lo - 1, false), &t.pack_frozen[lo], &t.n_pack_frozen[lo], 8);
-    put(net.pack_table(lo, 4, true), &t.pack_train[lo], &t.n_pack_train[lo], 8);
+    size_t row = 0;
+    while (layout[row] < net.stage_begin[lo]) row += kLayoutCols;
+    put(std::vector<long long>(layout.begin() + row, layout.end()), &t.layout_train[lo],
+        &t.n_layout_train[lo], kLayoutCols);
     put(sgd_rest_table(net, lo, &t.sgd_rest_max[lo]), &t.sgd_rest[lo], &t.n_sgd_rest[lo], 2);
     std::vector<long long> pr;
     for (const ConvL& c : net.conv)
@@ -1097,15 +1103,14 @@ static hipError_t build_cache(const Net& net, const Geo& g, const void* shadow, 
 static hipError_t job_setup(TrainJob& j) {
   const Net& net = *j.net;
   const Tables& t = *j.tabs;
-  EKYA_HIP(permute_weights(j.weights, j.master, t.permute, t.n_permute, net.total, 1, j.st));
+  EKYA_HIP(weights_to_internal(j.dt, j.weights, j.master, j.master, t.layout, t.n_layout, kMaxTaps,
+                               j.shadow, j.st));
+  EKYA_HIP(pack_crsk(j.dt, j.weights, t.layout_train[j.lowest], t.n_layout_train[j.lowest], j.shadow,
+                     j.st));
   EKYA_HIP(hipMemsetAsync(j.grad, 0, net.total * sizeof(float), j.st));
   EKYA_HIP(hipMemsetAsync(j.mom, 0, net.total * sizeof(float), j.st));
   EKYA_HIP(hipMemsetAsync(j.hcount, 0, j.epochs * sizeof(int32_t), j.st));
   EKYA_HIP(bn_fold(j.master, t.fold_all, t.n_fold_all, j.fold, j.st));
-  EKYA_HIP(pack_conv_weights(j.dt, j.master, t.pack_frozen[j.lowest], t.n_pack_frozen[j.lowest],
-                             j.shadow, j.st));
-  EKYA_HIP(pack_conv_weights(j.dt, j.master, t.pack_train[j.lowest], t.n_pack_train[j.lowest],
-                             j.shadow, j.st));
   EKYA_HIP(hipMemcpyAsync(j.d_order, j.h_order.data(), j.h_order.size() * sizeof(int32_t),
                           hipMemcpyHostToDevice, j.st));
   EKYA_HIP(hipMemcpyAsync(j.d_fidx, j.h_fidx.data(), j.h_fidx.size() * sizeof(int32_t),
@@ -1425,8 +1430,8 @@ ekya_status run_retrain(Ctx& c, float* weights, int k, const void* frames, const
     EKYA_HIP(hipEventRecord(p1, stream));
     EKYA_HIP(job_epochs(j));
     // write back: internal -> canonical (frozen parts round-trip exactly)
-    EKYA_HIP(permute_weights(j.master, weights, c.tabs[dt].permute, c.tabs[dt].n_permute,
-                             net.total, 0, stream));
+    EKYA_HIP(weights_to_canonical(j.master, weights, c.tabs[dt].layout, c.tabs[dt].n_layout,
+                                  kMaxTaps, stream));
     return hipSuccess;
   };
   hipError_t he = run();
@@ -1600,9 +1605,9 @@ ekya_status run_profile(Ctx& c, const float* weights, const ekya_profile_cfg* cf
   // caches: the frozen prefix of the starting weights, built once per depth on s0
   const Tables& t = c.tabs[dt];
   auto build = [&]() -> hipError_t {
-    EKYA_HIP(permute_weights(weights, pmaster, t.permute, t.n_permute, net.total, 1, s0));
+    EKYA_HIP(weights_to_internal(dt, weights, nullptr, pmaster, t.layout, t.n_layout, kMaxTaps,
+                                 pshadow, s0));
     EKYA_HIP(bn_fold(pmaster, t.fold_all, t.n_fold_all, pfold, s0));
-    EKYA_HIP(pack_conv_weights(dt, pmaster, t.pack_all, t.n_pack_all, pshadow, s0));
     if (!caches.empty())
       EKYA_HIP(hipMemcpyAsync(d_S, S.data(), S.size() * sizeof(int32_t), hipMemcpyHostToDevice, s0));
     for (auto& ci : caches) {
@@ -1720,15 +1725,6 @@ size_t infer_workspace_bytes(const Net& net, int resolution) {
   return a.used;
 }
 
-// Inference weights from internal-layout fp32 weights: folded eval-mode
-// BatchNorm and the low-precision convolution weights.
-static hipError_t prepare_inference(const Net& net, const Tables& t, const float* master,
-                                    float* fold, void* shadow, hipStream_t stream) {
-  EKYA_HIP(bn_fold(master, t.fold_all, t.n_fold_all, fold, stream));
-  EKYA_HIP(pack_conv_weights(net.dt, master, t.pack_all, t.n_pack_all, shadow, stream));
-  return hipSuccess;
-}
-
 // Classify n frames with prepared weights, chunk by chunk.
 static hipError_t infer_frames(const Net& net, const Geo& geo, const float* master,
                                const float* fold, const void* shadow, const void* frames, int n,
@@ -1785,8 +1781,9 @@ ekya_status run_infer(Ctx& c, const float* weights, const void* frames, int n, i
   plan_infer(real, net, geo, resolution, ib);
   const Tables& t = c.tabs[dt];
   auto run = [&]() -> hipError_t {
-    EKYA_HIP(permute_weights(weights, ib.master, t.permute, t.n_permute, net.total, 1, stream));
-    EKYA_HIP(prepare_inference(net, t, ib.master, ib.fold, ib.shadow, stream));
+    EKYA_HIP(weights_to_internal(dt, weights, nullptr, ib.master, t.layout, t.n_layout, kMaxTaps,
+                                 ib.shadow, stream));
+    EKYA_HIP(bn_fold(ib.master, t.fold_all, t.n_fold_all, ib.fold, stream));
     return infer_frames(net, geo, ib.master, ib.fold, ib.shadow, frames, n, H, W, resolution,
                         labels_out, ib, stream);
   };
@@ -1867,13 +1864,16 @@ hipError_t model_load(Model& m, const float* canonical, const float* internal, h
   for (auto& u : sl.uses) EKYA_HIP(hipStreamWaitEvent(stream, u.second, 0));
   for (auto& u : sl.uses) m.pool.push_back(u.second);
   sl.uses.clear();
-  if (canonical)
-    EKYA_HIP(permute_weights(canonical, sl.master, m.tabs.permute, m.tabs.n_permute, m.net.total,
-                             1, stream));
-  else
+  if (canonical) {
+    EKYA_HIP(weights_to_internal(m.dt, canonical, sl.master, sl.master, m.tabs.layout,
+                                 m.tabs.n_layout, kMaxTaps, sl.shadow, stream));
+  } else {
     EKYA_HIP(hipMemcpyAsync(sl.master, internal, m.net.total * sizeof(float),
                             hipMemcpyDeviceToDevice, stream));
-  EKYA_HIP(prepare_inference(m.net, m.tabs, sl.master, sl.fold, sl.shadow, stream));
+    EKYA_HIP(pack_conv_weights(m.dt, sl.master, m.tabs.pack_all, m.tabs.n_pack_all, sl.shadow,
+                               stream));
+  }
+  EKYA_HIP(bn_fold(sl.master, m.tabs.fold_all, m.tabs.n_fold_all, sl.fold, stream));
   EKYA_HIP(hipEventRecord(sl.ready, stream));
   sl.version = m.next_version++;
   m.current = s;
@@ -1889,8 +1889,8 @@ hipError_t model_export(Model& m, float* canonical_out, hipStream_t stream, uint
   EKYA_HIP(hipSetDevice(m.device));
   ModelSlot& sl = m.slot[m.current];
   EKYA_HIP(hipStreamWaitEvent(stream, sl.ready, 0));
-  EKYA_HIP(permute_weights(sl.master, canonical_out, m.tabs.permute, m.tabs.n_permute,
-                           m.net.total, 0, stream));
+  EKYA_HIP(weights_to_canonical(sl.master, canonical_out, m.tabs.layout, m.tabs.n_layout, kMaxTaps,
+                                stream));
   EKYA_HIP(model_note_use(m, m.current, stream));
   if (version) *version = sl.version;
   return hipSuccess;

@@ -37,8 +37,8 @@ struct Arena {
 // Device copies of the per-network tables the kernels read.
 struct Tables {
   DeviceBuf buf;
-  const long long* permute = nullptr;
-  int n_permute = 0;
+  const long long* layout = nullptr;  // every tensor
+  int n_layout = 0;
   const long long* fold_all = nullptr;
   int n_fold_all = 0;
   const long long* pack_all = nullptr;  // every conv, [K][R][S][C] shadow only
@@ -46,10 +46,8 @@ struct Tables {
   // per lowest trainable stage (0..5)
   const long long* fold_train[6] = {nullptr};
   int n_fold_train[6] = {0};
-  const long long* pack_frozen[6] = {nullptr};
-  int n_pack_frozen[6] = {0};
-  const long long* pack_train[6] = {nullptr};
-  int n_pack_train[6] = {0};
+  const long long* layout_train[6] = {nullptr};  // the rows of `layout` from that stage on
+  int n_layout_train[6] = {0};
   // step-end SGD ranges (offset, length) and repacking of the parameters
   // without a fused per-convolution update
   const long long* sgd_rest[6] = {nullptr};
