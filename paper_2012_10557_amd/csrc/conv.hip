@@ -3076,6 +3076,9 @@ hipError_t conv_fwd_dma(const ConvGeom& g, const void* x, const void* w, void* y
   if (conv64_ok(g) && !(sink && !sink->bwd && bn_fold_path(npix, g.K)))
     return conv64(g, false, x, w, y, epi, stream);
   DmaPlan p = plan_dma(g.K, npix, ns, ws != nullptr);
+  // (a sink's BatchNorm partials come from the kernels below)
+  if (!sink && conv_few_ok(DT_BF16, g))
+    return conv_few_fwd(DT_BF16, g, x, w, y, epi, stream);
   if (p.splits > 1 && (size_t)p.splits * npix * g.K > ws_floats) p = {p.bm, p.bn, 1, ns, p.ws};
   DmaFwdArgs a{g, (const bf16*)x, (const bf16*)w, (bf16*)y, epi, SplitOut{ws, p.splits, p.sps}, 0, 0};
   const bool plain = !epi.scale && !epi.shift && !epi.res && !epi.relu;
@@ -3222,6 +3225,8 @@ hipError_t conv_fwd_t(const ConvGeom& g, const void* x, const void* w, void* y,
     }
     return e;
   }
+  if (sizeof(T) == 4 && conv_few_ok(DT_F32, g))
+    return conv_few_fwd(DT_F32, g, x, w, y, epi, stream);
   const bool ut = g.C % (KU_MAIN * E) == 0;
   const int ns = cdiv(g.R * g.S * g.C, KU_MAIN * E);
   const long long npix = (long long)g.N * g.P * g.Q;

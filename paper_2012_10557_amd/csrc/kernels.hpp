@@ -90,6 +90,11 @@ struct BnStatsSink {
   bool done = false;
   int rows = 0;  // rows per chunk of the partials when done (64 or 128)
 };
+// Forward convolutions with few output pixels in one launch, without split
+// scratch (conv_few_ok: shapes it takes).  Same arguments as conv_fwd.
+bool conv_few_ok(int dt, const ConvGeom& g);
+hipError_t conv_few_fwd(int dt, const ConvGeom& g, const void* x, const void* w, void* y,
+                        const ConvEpilogue& epi, hipStream_t stream);
 
 // y[N,P,Q,K] = conv(x[N,H,W,C], w[K,R,S,C]) with the epilogue.  `ws` (fp32,
 // ws_floats) holds split-reduction partials when the output has too few tiles
