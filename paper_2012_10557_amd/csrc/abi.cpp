@@ -4,6 +4,7 @@
 #include <cmath>
 #include <cstdio>
 #include <cstring>
+#include <initializer_list>
 #include <iterator>
 #include <mutex>
 #include <new>
@@ -303,16 +304,24 @@ int ekya_epoch_order(int n, uint64_t seed, int epoch, int32_t* order_out) {
 // ------------------------------------------------------------------ ops
 namespace {
 
+// A call's temporaries, carved from one allocation (an allocation and its
+// release cost a call about 10 us).
 struct Tmp {
-  std::vector<void*> ptrs;
+  char* base = nullptr;
+  size_t cap = 0, used = 0;
   ~Tmp() {
-    for (void* p : ptrs) (void)hipFree(p);
+    if (base) (void)hipFree(base);
+  }
+  static size_t padded(size_t bytes) { return (bytes + 64 + 255) & ~(size_t)255; }
+  hipError_t reserve(std::initializer_list<size_t> bytes) {
+    for (size_t n : bytes) cap += padded(n);
+    return hipMalloc((void**)&base, cap);
   }
   template <typename T> T* get(size_t n) {
-    void* p = nullptr;
-    if (hipMalloc(&p, std::max<size_t>(n, 1) * sizeof(T) + 64) != hipSuccess) return nullptr;
-    ptrs.push_back(p);
-    return reinterpret_cast<T*>(p);
+    const size_t need = padded(n * sizeof(T));
+    if (!base || used + need > cap) return nullptr;
+    used += need;
+    return reinterpret_cast<T*>(base + used - need);
   }
 };
 
@@ -322,29 +331,45 @@ bool chan_ok(int dt, int C, bool allow3) {
 }
 
 // fp32 [K][C][R][S] weights in one of the kernels' low-precision layouts:
-// [K][RS][Cp] (crsk false) or [C][RS][K].
-hipError_t pack_one(int dt, const float* w, int K, int C, int R, int S, int Cp, bool crsk, Tmp& tmp,
-                    void** out, hipStream_t st) {
+// [K][RS][Cp] (crsk false) or [C][RS][K].  pack_bytes: what it takes from tmp.
+struct PackPlan {
+  long long n;  // elements of a layout
+  bool both;    // [C][RS][K] through the [K][RS][C] layouts (long filters)
+  size_t table, master, out;
+};
+PackPlan plan_pack(int dt, int K, int R, int S, int Cp, bool crsk) {
+  PackPlan p{};
+  p.n = (long long)K * R * S * Cp;
+  p.both = crsk && !ekya::pack_crsk_ok(R * S);
+  p.table = p.both ? 8 * sizeof(long long) : 0;
+  p.master = p.both ? p.n * sizeof(float) : 0;
+  p.out = (p.both ? 2 : 1) * p.n * ekya::dtype_size(dt);
+  return p;
+}
+hipError_t pack_one(int dt, const float* w, int K, int C, int R, int S, int Cp, bool crsk,
+                    const PackPlan& p, Tmp& tmp, void** out, hipStream_t st) {
   const long long RS = (long long)R * S;
-  const size_t es = ekya::dtype_size(dt);
-  const long long n = K * RS * Cp;
-  const bool both = crsk && !ekya::pack_crsk_ok((int)RS);  // through the [K][RS][C] layouts
-  long long* tab = tmp.get<long long>(16);
-  char* sh = tmp.get<char>((both ? 2 : 1) * n * es);
-  float* m = both ? tmp.get<float>(n) : nullptr;
-  if (!tab || !sh || (both && !m)) return hipErrorOutOfMemory;
+  long long* tab = tmp.get<long long>(p.table / sizeof(long long));
+  float* m = tmp.get<float>(p.master / sizeof(float));
+  char* sh = tmp.get<char>(p.out);
+  if (!tab || !m || !sh) return hipErrorOutOfMemory;
   *out = sh;
-  if (both) {
-    const long long h[15] = {0, K, C, RS, Cp, -1, -1, 0, K, R, S, C, Cp, 0, n};
-    *out = sh + n * es;
+  if (p.both) {
+    const long long h[8] = {0, K, R, S, C, Cp, 0, p.n};
+    *out = sh + p.n * ekya::dtype_size(dt);
     EKYA_HIP(hipMemcpy(tab, h, sizeof(h), hipMemcpyHostToDevice));
-    EKYA_HIP(ekya::weights_to_internal(dt, w, m, m, tab, 1, (int)RS, nullptr, st));
-    return ekya::pack_conv_weights(dt, m, tab + 7, 1, sh, st);
+    const auto row = ekya::layout_of({0, K, C, RS, Cp, -1, -1});
+    EKYA_HIP(ekya::weights_to_internal(dt, w, m, m, row, nullptr, st));
+    return ekya::pack_conv_weights(dt, m, tab, 1, sh, st);
   }
-  const long long h[7] = {0, K, C, RS, Cp, crsk ? -1 : 0, crsk ? 0 : -1};
-  EKYA_HIP(hipMemcpy(tab, h, sizeof(h), hipMemcpyHostToDevice));
-  if (crsk) return ekya::pack_crsk(dt, w, tab, 1, sh, st);
-  return ekya::weights_to_internal(dt, w, nullptr, nullptr, tab, 1, (int)RS, sh, st);
+  const auto row = ekya::layout_of({0, K, C, RS, Cp, crsk ? -1 : 0, crsk ? 0 : -1});
+  return crsk ? ekya::pack_crsk(dt, w, row, sh, st)
+              : ekya::weights_to_internal(dt, w, nullptr, nullptr, row, sh, st);
+}
+
+// Bytes of an image padded to the 16-byte unit (0: C needs no padding).
+size_t pad_bytes(int dt, int N, int H, int W, int C) {
+  return C == 3 ? (size_t)N * H * W * ekya::dtype_vec(dt) * ekya::dtype_size(dt) : 0;
 }
 
 hipError_t pad_input(int dt, const void* x, int N, int H, int W, int C, int& Cp, Tmp& tmp,
@@ -353,7 +378,7 @@ hipError_t pad_input(int dt, const void* x, int N, int H, int W, int C, int& Cp,
   *xp = x;
   if (C != 3) return hipSuccess;
   Cp = ekya::dtype_vec(dt);
-  void* p = tmp.get<char>((size_t)N * H * W * Cp * ekya::dtype_size(dt));
+  void* p = tmp.get<char>(pad_bytes(dt, N, H, W, C));
   if (!p) return hipErrorOutOfMemory;
   EKYA_HIP(ekya::frames_to_padded(dt, x, nullptr, N, H, W, Cp, p, st));
   *xp = p;
@@ -395,15 +420,17 @@ ekya_status ekya_op_conv2d(int precision, const void* x, int N, int H, int W, in
     return fail(nullptr, EKYA_ERR_INVALID_ARG, "invalid conv2d arguments");
   hipStream_t st = (hipStream_t)stream;
   Tmp tmp;
-  int Cp;
+  int Cp = C == 3 ? ekya::dtype_vec(precision) : C;
   const void* xp;
   void* krsc;
-  hipError_t e = pad_input(precision, x, N, H, W, C, Cp, tmp, &xp, st);
-  if (e == hipSuccess) e = pack_one(precision, w, K, C, R, S, Cp, false, tmp, &krsc, st);
   const ekya::ConvGeom g = make_geom(N, H, W, Cp, K, R, S, stride, pad);
+  const PackPlan pp = plan_pack(precision, K, R, S, Cp, false);
   const size_t wsf = ekya::conv_split_workspace_floats(precision, g, false);
+  hipError_t e = tmp.reserve({pad_bytes(precision, N, H, W, C), pp.table, pp.master, pp.out,
+                              wsf * sizeof(float)});
+  if (e == hipSuccess) e = pad_input(precision, x, N, H, W, C, Cp, tmp, &xp, st);
+  if (e == hipSuccess) e = pack_one(precision, w, K, C, R, S, Cp, false, pp, tmp, &krsc, st);
   float* ws = wsf ? tmp.get<float>(wsf) : nullptr;
-  if (wsf && !ws) e = hipErrorOutOfMemory;
   if (e == hipSuccess) e = ekya::conv_fwd(precision, g, xp, krsc, y, ekya::ConvEpilogue(), ws, wsf, st);
   return sync_status(st, e);
 }
@@ -417,11 +444,12 @@ ekya_status ekya_op_conv2d_dgrad(int precision, const void* dy, const float* w, 
   hipStream_t st = (hipStream_t)stream;
   Tmp tmp;
   void* crsk;
-  hipError_t e = pack_one(precision, w, K, C, R, S, C, true, tmp, &crsk, st);
   const ekya::ConvGeom g = make_geom(N, H, W, C, K, R, S, stride, pad);
+  const PackPlan pp = plan_pack(precision, K, R, S, C, true);
   const size_t wsf = ekya::conv_split_workspace_floats(precision, g, true);
+  hipError_t e = tmp.reserve({pp.table, pp.master, pp.out, wsf * sizeof(float)});
+  if (e == hipSuccess) e = pack_one(precision, w, K, C, R, S, C, true, pp, tmp, &crsk, st);
   float* ws = wsf ? tmp.get<float>(wsf) : nullptr;
-  if (wsf && !ws) e = hipErrorOutOfMemory;
   if (e == hipSuccess) e = ekya::conv_dgrad(precision, g, dy, crsk, dx, nullptr, ws, wsf, st);
   return sync_status(st, e);
 }
@@ -433,21 +461,19 @@ ekya_status ekya_op_conv2d_wgrad(int precision, const void* x, const void* dy, i
     return fail(nullptr, EKYA_ERR_INVALID_ARG, "invalid conv2d_wgrad arguments");
   hipStream_t st = (hipStream_t)stream;
   Tmp tmp;
-  int Cp;
+  int Cp = C == 3 ? ekya::dtype_vec(precision) : C;
   const void* xp;
-  hipError_t e = pad_input(precision, x, N, H, W, C, Cp, tmp, &xp, st);
   ekya::ConvGeom g = make_geom(N, H, W, Cp, K, R, S, stride, pad);
   g.C0 = C;  // the plan (and so its scratch) depends on the real channel count
-  float* part = tmp.get<float>(ekya::conv_wgrad_workspace_floats(precision, g));
-  float* krsc = tmp.get<float>((size_t)K * R * S * C);
-  long long* tab = tmp.get<long long>(8);
-  if (!part || !krsc || !tab) e = hipErrorOutOfMemory;
+  const size_t pf = ekya::conv_wgrad_workspace_floats(precision, g), nw = (size_t)K * R * S * C;
+  hipError_t e = tmp.reserve({pad_bytes(precision, N, H, W, C), pf * sizeof(float),
+                              nw * sizeof(float)});
+  if (e == hipSuccess) e = pad_input(precision, x, N, H, W, C, Cp, tmp, &xp, st);
+  float* part = tmp.get<float>(pf);
+  float* krsc = tmp.get<float>(nw);
   if (e == hipSuccess) e = ekya::conv_wgrad(precision, g, xp, dy, part, krsc, C, st);
-  if (e == hipSuccess) {
-    long long h[7] = {0, K, C, (long long)R * S, C, -1, -1};
-    e = hipMemcpy(tab, h, sizeof(h), hipMemcpyHostToDevice);
-  }
-  if (e == hipSuccess) e = ekya::weights_to_canonical(krsc, dw, tab, 1, R * S, st);
+  if (e == hipSuccess)
+    e = ekya::weights_to_canonical(krsc, dw, ekya::layout_of({0, K, C, (long long)R * S, C, -1, -1}), st);
   return sync_status(st, e);
 }
 
@@ -461,9 +487,10 @@ ekya_status ekya_op_batchnorm_train(int precision, const void* z, long long M, i
     return fail(nullptr, EKYA_ERR_INVALID_ARG, "invalid batchnorm_train arguments");
   hipStream_t st = (hipStream_t)stream;
   Tmp tmp;
-  float* part = tmp.get<float>(ekya::bn_partials_floats(M, C));
+  const size_t pf = ekya::bn_partials_floats(M, C);
+  hipError_t e = tmp.reserve({pf * sizeof(float), 2 * (size_t)C * sizeof(float)});
+  float* part = tmp.get<float>(pf);
   float* ss = tmp.get<float>(2 * (size_t)C);
-  hipError_t e = (part && ss) ? hipSuccess : hipErrorOutOfMemory;
   if (e == hipSuccess)
     e = ekya::bn_train_forward(precision, z, M, C, gamma, beta, running_mean, running_var,
                                mean_out, invstd_out, ss, ss + C, nullptr, relu, y, part, st);
@@ -540,8 +567,9 @@ ekya_status ekya_op_batchnorm_backward(int precision, const void* dy, const void
     return fail(nullptr, EKYA_ERR_INVALID_ARG, "invalid batchnorm_backward arguments");
   hipStream_t st = (hipStream_t)stream;
   Tmp tmp;
-  float* part = tmp.get<float>(ekya::bn_partials_floats(M, C));
-  hipError_t e = part ? hipSuccess : hipErrorOutOfMemory;
+  const size_t pf = ekya::bn_partials_floats(M, C);
+  hipError_t e = tmp.reserve({pf * sizeof(float)});
+  float* part = tmp.get<float>(pf);
   if (e == hipSuccess)
     e = ekya::bn_backward(precision, dy, y_relu, z, M, C, gamma, mean, invstd, dgamma, dbeta, dz,
                           nullptr, part, st);

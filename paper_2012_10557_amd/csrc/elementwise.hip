@@ -1525,9 +1525,19 @@ __global__ __launch_bounds__(256) void head_bwd_kernel(const float* z, const int
                                                        const int32_t* idx, int N, int J,
                                                        const float* f, const float* W, int I,
                                                        float* dW, float* db, T* dout, int HW,
-                                                       float* out, HeadBnArgs bp) {
+                                                       float* out, HeadBnArgs bp, HeadSgd sgd) {
   constexpr int E = Elt<T>::E;
   const int t = threadIdx.x;
+  // a gradient element, or with `sgd` its momentum step (as sgd_ranges_kernel)
+  auto leave = [&](float* grad, float* w, float* v, long long o, float g) {
+    if (!sgd.w) {
+      grad[o] = g;
+      return;
+    }
+    const float vn = sgd.mu * v[o] + g;
+    v[o] = vn;
+    w[o] = w[o] - sgd.lr * vn;
+  };
   __shared__ float rdz[256][HEAD_JMAX];
   __shared__ float rl[256];
   __shared__ int rc[256], rb[256];
@@ -1588,9 +1598,10 @@ __global__ __launch_bounds__(256) void head_bwd_kernel(const float* z, const int
     __syncthreads();
     if (sl == 0 && i < I)
       for (int j = 0; j < J; ++j)
-        dW[(long long)j * I + i] = ((part[0][j][il] + part[1][j][il]) + part[2][j][il]) + part[3][j][il];
+        leave(dW, sgd.w, sgd.wv, (long long)j * I + i,
+              ((part[0][j][il] + part[1][j][il]) + part[2][j][il]) + part[3][j][il]);
     if (blockIdx.x == 0) {
-      if (t < J) db[t] = dsum;
+      if (t < J) leave(db, sgd.b, sgd.bv, t, dsum);
       if (t == 64) out[0] = L / (float)N;
       if (t == 128) out[1] = (float)C;
       if (t == 192) out[2] = (float)bad;
@@ -2320,8 +2331,11 @@ bool head_backward_fused(int J, int I) { return J <= HEAD_JMAX && I <= 64 * HEAD
 
 hipError_t head_backward(int dt, const float* z, const int32_t* labels, const int32_t* idx, int N,
                          int J, const float* f, const float* W, int I, float* dW, float* db,
-                         void* dout, int HW, float* out, hipStream_t stream, HeadBnSink* bn) {
+                         void* dout, int HW, float* out, hipStream_t stream, HeadBnSink* bn,
+                         const HeadSgd* step) {
   if (bn) bn->rows = 0;
+  if (step && dout) return hipErrorInvalidValue;  // dout reads W while dW's blocks would change it
+  const HeadSgd sgd = step ? *step : HeadSgd{};
   if (!head_backward_fused(J, I) || I % dtype_vec(dt) != 0 || 256 % (I / dtype_vec(dt)) != 0)
     return hipErrorInvalidValue;
   const long long Mr = (long long)N * HW;
@@ -2338,10 +2352,10 @@ hipError_t head_backward(int dt, const float* z, const int32_t* labels, const in
     using T = std::remove_pointer_t<decltype(tp)>;
     if (bnp)
       hipLaunchKernelGGL((head_bwd_kernel<T, true>), dim3(HEAD_WB + dblocks), dim3(256), 0, stream,
-                         z, labels, idx, N, J, f, W, I, dW, db, (T*)dout, HW, out, ha);
+                         z, labels, idx, N, J, f, W, I, dW, db, (T*)dout, HW, out, ha, sgd);
     else
       hipLaunchKernelGGL((head_bwd_kernel<T, false>), dim3(HEAD_WB + dblocks), dim3(256), 0,
-                         stream, z, labels, idx, N, J, f, W, I, dW, db, (T*)dout, HW, out, ha);
+                         stream, z, labels, idx, N, J, f, W, I, dW, db, (T*)dout, HW, out, ha, sgd);
   }), "head_bwd", (double)Mr * I * dtype_size(dt) * (bnp ? 3 : 1) + (double)N * I * 4);
   if (e == hipSuccess && bnp) bn->rows = 64;
   return e;

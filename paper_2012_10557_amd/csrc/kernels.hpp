@@ -286,10 +286,17 @@ struct HeadBnSink {
   int rows = 0;
 };
 bool head_backward_fused(int J, int I);
+// step (without dout): in place of dW and db, the momentum step of the
+// classifier itself, v = mu v + g, w = w - lr v.
+struct HeadSgd {
+  float *w = nullptr, *wv = nullptr, *b = nullptr, *bv = nullptr;
+  float lr = 0.f, mu = 0.f;
+};
 hipError_t head_backward(int dt, const float* z, const int32_t* labels, const int32_t* idx, int N,
                          int J, const float* f, const float* W, int I, float* dW, float* db,
                          void* dout, int HW, float* out, hipStream_t stream,
-                         HeadBnSink* bn = nullptr);
+                         HeadBnSink* bn = nullptr,
+                         const HeadSgd* step = nullptr);
 // Count of rows whose argmax matches the label, accumulated into *count.
 hipError_t count_correct(const float* z, const int32_t* labels, int N, int J, int32_t* count,
                          hipStream_t stream);
@@ -338,22 +345,36 @@ hipError_t cast_from_f32(int dt, const float* src, long long n, void* dst, hipSt
 hipError_t pack_conv_weights(int dt, const float* master, const long long* tab, int n,
                              void* shadow, hipStream_t stream);
 // Between the canonical layout (convolutions [K][C][RS]) and the internal one
-// ([K][RS][C]).  Table row per tensor: off, K, C, RS, Cp, krsc_off, crsk_off
-// (offsets of its low-precision copies in elements of dt, -1: none), or off,
-// n, 1, 1, 1, -1, -1 for anything but a convolution.  max_taps: the largest
-// RS of the table.  weights_to_internal writes `master` (null: none) for the
-// rows with a krsc copy, `rest` (the same array, or with master null where
-// the others go) for those without, and with `shadow` the [K][RS][Cp]
-// copies in the same pass.
+// ([K][RS][C]).  A row per tensor: offset, sizes and the offsets of its
+// low-precision copies in elements of dt (-1: none); K = n, C = RS = Cp = 1
+// for anything but a convolution.
+struct LayoutRow {
+  long long off, K, C, RS, Cp, krsc, crsk;
+};
+struct LayoutTable {
+  const LayoutRow* rows = nullptr;  // on the device; null: the one row `one`
+  int n = 0;
+  int max_taps = 0;  // the largest RS
+  LayoutRow one{};
+};
+inline LayoutTable layout_of(const LayoutRow& r) {
+  LayoutTable t;
+  t.n = 1;
+  t.max_taps = (int)r.RS;
+  t.one = r;
+  return t;
+}
+// Writes `master` (null: none) for the rows with a krsc copy, `rest` (the same
+// array, or with master null where the others go) for those without, and with
+// `shadow` the [K][RS][Cp] copies in the same pass.
 hipError_t weights_to_internal(int dt, const float* canonical, float* master, float* rest,
-                               const long long* tab, int n, int max_taps, void* shadow,
-                               hipStream_t stream);
-hipError_t weights_to_canonical(const float* master, float* canonical, const long long* tab, int n,
-                                int max_taps, hipStream_t stream);
+                               const LayoutTable& tab, void* shadow, hipStream_t stream);
+hipError_t weights_to_canonical(const float* master, float* canonical, const LayoutTable& tab,
+                                hipStream_t stream);
 // The [C][RS][K] copies of the rows that have one, from the canonical array
 // (pack_crsk_ok: filters it takes).
 bool pack_crsk_ok(int taps);
-hipError_t pack_crsk(int dt, const float* canonical, const long long* tab, int n, void* shadow,
+hipError_t pack_crsk(int dt, const float* canonical, const LayoutTable& tab, void* shadow,
                      hipStream_t stream);
 
 // ------------------------------------------------------------- diagnostics

@@ -43,6 +43,37 @@ void DeviceBuf::release() {
   cap = 0;
 }
 
+// Every event here orders work between streams of one device (or times it);
+// the host reads results only after a stream synchronisation.  Without the
+// system-scope fence a recorded event costs its stream a shorter bubble.
+hipError_t EventPool::take(bool timing, hipEvent_t* e) {
+  {
+    std::lock_guard<std::mutex> lk(mu);
+    std::vector<hipEvent_t>& v = timing ? timed : plain;
+    if (!v.empty()) {
+      *e = v.back();
+      v.pop_back();
+      return hipSuccess;
+    }
+  }
+  return hipEventCreateWithFlags(
+      e, (timing ? 0 : hipEventDisableTiming) | hipEventDisableSystemFence);
+}
+
+void EventPool::give(bool timing, hipEvent_t& e) {
+  if (!e) return;
+  std::lock_guard<std::mutex> lk(mu);
+  (timing ? timed : plain).push_back(e);
+  e = nullptr;
+}
+
+void EventPool::release() {
+  for (auto* v : {&timed, &plain}) {
+    for (hipEvent_t e : *v) (void)hipEventDestroy(e);
+    v->clear();
+  }
+}
+
 // Convolutions whose momentum step runs right after their weight gradient
 // (conv_weight_update from the split partials); the others' gradients go
 // through the gradient buffer and the step-end SGD.
@@ -78,8 +109,7 @@ static std::vector<long long> sgd_rest_table(const Net& net, int lo, long long* 
 }
 
 // ----------------------------------------------------------------- tables
-constexpr int kLayoutCols = 7;
-constexpr int kMaxTaps = 49;  // the stem's 7 x 7 filter
+constexpr int kLayoutCols = sizeof(LayoutRow) / sizeof(long long);
 
 static hipError_t upload_tables(const Net& net, Tables& t) {
   std::vector<long long> all;
@@ -90,15 +120,12 @@ static hipError_t upload_tables(const Net& net, Tables& t) {
     all.insert(all.end(), v.begin(), v.end());
   };
   const std::vector<long long> layout = net.layout_table();
-  put(layout, &t.layout, &t.n_layout, kLayoutCols);
+  const long long* layout_at = nullptr;
+  put(layout, &layout_at, &t.layout.n, kLayoutCols);
   put(net.fold_table(0, 5), &t.fold_all, &t.n_fold_all, 6);
   put(net.pack_table(0, 4, false), &t.pack_all, &t.n_pack_all, 8);
   for (int lo = 0; lo <= 5; ++lo) {
     put(net.fold_table(lo, 5), &t.fold_train[lo], &t.n_fold_train[lo], 6);
-    size_t row = 0;
-    while (layout[row] < net.stage_begin[lo]) row += kLayoutCols;
-    put(std::vector<long long>(layout.begin() + row, layout.end()), &t.layout_train[lo],
-        &t.n_layout_train[lo], kLayoutCols);
     put(sgd_rest_table(net, lo, &t.sgd_rest_max[lo]), &t.sgd_rest[lo], &t.n_sgd_rest[lo], 2);
     std::vector<long long> pr;
     for (const ConvL& c : net.conv)
@@ -109,6 +136,15 @@ static hipError_t upload_tables(const Net& net, Tables& t) {
   EKYA_HIP(t.buf.alloc(all.size() * sizeof(long long) + 16));
   EKYA_HIP(hipMemcpy(t.buf.p, all.data(), all.size() * sizeof(long long), hipMemcpyHostToDevice));
   for (auto& f : fix) *f.first = reinterpret_cast<const long long*>(t.buf.p) + f.second;
+  t.layout.rows = reinterpret_cast<const LayoutRow*>(layout_at);
+  t.layout.max_taps = 49;  // the stem's 7 x 7 filter
+  for (int lo = 0; lo <= 5; ++lo) {
+    int row = 0;
+    while (layout[row * kLayoutCols] < net.stage_begin[lo]) ++row;
+    t.layout_train[lo] = t.layout;
+    t.layout_train[lo].rows += row;
+    t.layout_train[lo].n -= row;
+  }
   return hipSuccess;
 }
 
@@ -191,6 +227,7 @@ void ctx_free(Ctx& c) {
   }
   if (c.last_done) (void)hipEventDestroy(c.last_done);
   c.last_done = nullptr;
+  c.events.release();
   c.ws.release();
   for (auto& t : c.tabs) t.buf.release();
 }
@@ -297,6 +334,9 @@ struct EvalBufs {
 
 static ConvGeom conv_geom(const Net& net, const Geo& g, int ci, int n);
 
+// Kinds of memoised scratch sizes (PlanMemo).
+enum ScratchKind { kScratchEval, kScratchTrain, kScratchWgrad, kScratchBn };
+
 static long long max_act_elems(const Net& net, const Geo& g, int lo, int hi) {
   long long m = 0;
   if (lo <= 0 && hi >= 0) m = std::max(m, (long long)g.sh * g.sw * 64);
@@ -321,13 +361,15 @@ static void plan_eval(Arena& a, const Net& net, const Geo& g, int lo, int hi, in
   b.logits = a.take<float>((size_t)cap * net.n_classes);
   // split-reduction scratch for every frame count a call may use, so that a
   // convolution's plan never depends on how large this scratch happens to be
-  size_t ws = 16;
-  for (size_t i = 0; i < net.conv.size(); ++i)
-    if (net.conv[i].stage >= lo && net.conv[i].stage <= hi)
-      for (int n = 1; n <= cap; ++n)
-        ws = std::max(ws, conv_split_workspace_floats(net.dt, conv_geom(net, g, (int)i, n), false));
-  b.ws_floats = ws;
-  b.ws = a.take<float>(ws);
+  b.ws_floats = a.memo->get({kScratchEval, net.dt, g.H, g.W, lo, hi, cap}, [&] {
+    size_t ws = 16;
+    for (size_t i = 0; i < net.conv.size(); ++i)
+      if (net.conv[i].stage >= lo && net.conv[i].stage <= hi)
+        for (int n = 1; n <= cap; ++n)
+          ws = std::max(ws, conv_split_workspace_floats(net.dt, conv_geom(net, g, (int)i, n), false));
+    return ws;
+  });
+  b.ws = a.take<float>(b.ws_floats);
 }
 
 static ConvGeom conv_geom(const Net& net, const Geo& g, int ci, int n) {
@@ -473,7 +515,8 @@ struct TrainJob {
   float *bn_mean = nullptr, *bn_invstd = nullptr, *bn_scale = nullptr, *bn_shift = nullptr;
   float* fold = nullptr;
   int32_t *d_order = nullptr, *d_fidx = nullptr;
-  void* x0 = nullptr;
+  void* x0 = nullptr;           // a batch's input (classifier only: an epoch's features)
+  const float* feat = nullptr;  // classifier only: the batch's features in x0
   void* stem_Z = nullptr;
   void* stem_A = nullptr;
   uint8_t* stem_arg = nullptr;
@@ -498,7 +541,8 @@ struct TrainJob {
   // blocks at full depth) plus the end join, the forward pass one per
   // projection shortcut; each half of the arrays holds more than that.
   static constexpr int kForks = 64;
-  hipEvent_t fork[kForks] = {nullptr};
+  EventPool* pool = nullptr;
+  hipEvent_t fork[kForks] = {nullptr};  // taken from the pool when first recorded
   hipEvent_t joined[kForks] = {nullptr};
   // joined[] index of the end-of-backward join that st has not waited for
   // yet (-1: none); see settle()
@@ -530,7 +574,13 @@ struct TrainJob {
 // data gradient is folded into conv1's, the end join
 static_assert(3 * 8 + 3 + 1 <= TrainJob::kForks / 2, "fork events for a full-depth backward pass");
 
-static size_t ws_floats(const TrainJob& j) {
+// Record one of the job's ordering events.
+static hipError_t record(const TrainJob& j, hipEvent_t& e, hipStream_t s) {
+  if (!e) EKYA_HIP(j.pool->take(false, &e));
+  return hipEventRecord(e, s);
+}
+
+static size_t ws_floats(const TrainJob& j) {  // (the memo's kScratchTrain)
   const Net& net = *j.net;
   size_t m = 0;
   for (size_t i = 0; i < net.conv.size(); ++i) {
@@ -573,6 +623,9 @@ static long long train_max_elems(const TrainJob& j) {
 // Assign every device buffer of a job (arena sizing pass when a.base == null).
 static void plan_job(Arena& a, TrainJob& j) {
   const Net& net = *j.net;
+  auto memo = [&](int kind, auto&& f) {
+    return a.memo->get({kind, j.dt, j.geo.H, j.geo.W, j.lowest, 4, j.B}, f);
+  };
   const size_t es = dtype_size(j.dt);
   const long long tb = net.stage_begin[j.lowest];
   j.master = a.take<float>(net.total);
@@ -593,7 +646,7 @@ static void plan_job(Arena& a, TrainJob& j) {
   j.d_fidx = a.take<int32_t>((size_t)j.epochs * j.n_s);
   const long long in_elems = j.geo.stage_in_elems(net, j.lowest);
   const size_t in_es = (j.lowest == 5) ? 4 : es;
-  j.x0 = a.take_bytes((size_t)j.B * in_elems * in_es);
+  j.x0 = a.take_bytes((size_t)(j.lowest == 5 ? j.n_s : j.B) * in_elems * in_es);
   j.acts.assign(net.blk.size(), BlockAct());
   if (j.lowest == 0) {
     j.stem_Z = a.take_bytes((size_t)j.B * j.geo.sh * j.geo.sw * 64 * es);
@@ -624,7 +677,8 @@ static void plan_job(Arena& a, TrainJob& j) {
       j.gzd[p] = a.take_bytes(gmax * es);
     }
     // st2 also runs the projection-shortcut convolutions of the forward pass
-    j.ws2_floats = std::max(wgrad_ws_floats(j), ws_floats(j));
+    j.ws2_floats = std::max(memo(kScratchWgrad, [&] { return wgrad_ws_floats(j); }),
+                            memo(kScratchTrain, [&] { return ws_floats(j); }));
     j.ws2 = a.take<float>(j.ws2_floats);
   }
   j.pooled = a.take<float>((size_t)j.B * 512);
@@ -635,17 +689,20 @@ static void plan_job(Arena& a, TrainJob& j) {
   }
   j.logits = a.take<float>((size_t)j.B * net.n_classes);
   j.dz = a.take<float>((size_t)j.B * net.n_classes);
-  j.ws_floats = ws_floats(j);
+  j.ws_floats = memo(kScratchTrain, [&] { return ws_floats(j); });
   j.ws = a.take<float>(j.ws_floats);
-  j.bn_ws_floats = 16;
-  for (size_t i = 0; i < net.conv.size(); ++i) {
-    const ConvL& c = net.conv[i];
-    if (c.stage < j.lowest || c.stage > 4) continue;
-    for (int n = 1; n <= j.B; ++n) {
-      const ConvGeom cg = conv_geom(net, j.geo, (int)i, n);
-      j.bn_ws_floats = std::max(j.bn_ws_floats, bn_partials_floats((long long)n * cg.P * cg.Q, c.cout));
+  j.bn_ws_floats = memo(kScratchBn, [&] {
+    size_t m = 16;
+    for (size_t i = 0; i < net.conv.size(); ++i) {
+      const ConvL& c = net.conv[i];
+      if (c.stage < j.lowest || c.stage > 4) continue;
+      for (int n = 1; n <= j.B; ++n) {
+        const ConvGeom cg = conv_geom(net, j.geo, (int)i, n);
+        m = std::max(m, bn_partials_floats((long long)n * cg.P * cg.Q, c.cout));
+      }
     }
-  }
+    return m;
+  });
   j.bn_ws = a.take<float>(j.bn_ws_floats);
   j.bn_ws2 = a.take<float>(j.bn_ws_floats);
   j.ce_out = a.take<float>((size_t)j.n_steps * 3);
@@ -667,13 +724,13 @@ static void plan_job(Arena& a, TrainJob& j) {
 
 static inline float* bnp(float* base, const BnL& b) { return base + b.st; }
 
-// Average pool (x: layer4's output; null: the pooled features in x0) and
+// Average pool (x: layer4's output; null: the pooled features in feat) and
 // the classifier: pooled and logits, or with a hidden layer the pooled
 // features, the hidden layer's ReLU activations and the logits.
 static hipError_t train_head_forward(TrainJob& j, int nb, const void* x) {
   const Net& net = *j.net;
   const int hw = j.geo.lh[4] * j.geo.lw[4];
-  const float* f = x ? nullptr : reinterpret_cast<const float*>(j.x0);
+  const float* f = x ? nullptr : j.feat;
   float* pooled = x ? j.pooled : nullptr;
   if (net.hidden == 0)
     return head_forward(j.dt, x, hw, f, j.master + net.fc_w, j.master + net.fc_b, nb, 512,
@@ -750,7 +807,7 @@ static hipError_t train_forward(TrainJob& j, int nb) {
       const bool side = b.cd >= 0 && two;
       if (side) {  // the block input is ready: fork before queueing the main branch
         if (fi < TrainJob::kForks / 2) return hipErrorInvalidValue;
-        EKYA_HIP(hipEventRecord(j.fork[fi], st));
+        EKYA_HIP(record(j, j.fork[fi], st));
       }
       EKYA_HIP(conv_fwd(dt, g1, t.X, shadow_at(net, j.shadow, net.conv[b.c1].sh_krsc), t.Z1,
                         ConvEpilogue(), j.ws, j.ws_floats, st, &sk));
@@ -764,7 +821,7 @@ static hipError_t train_forward(TrainJob& j, int nb) {
         EKYA_HIP(bn_train_on(net.conv[b.cd].bn, t.Zd, M, nullptr, 0, j.g[0],
                              skd.done ? skd.rows : 0, j.bn_ws2, q));
         if (side) {
-          EKYA_HIP(hipEventRecord(j.joined[fi], q));
+          EKYA_HIP(record(j, j.joined[fi], q));
           joined = fi--;
         }
         res = j.g[0];
@@ -783,13 +840,19 @@ static hipError_t train_forward(TrainJob& j, int nb) {
   return train_head_forward(j, nb, nullptr);
 }
 
+// Classifier-only jobs whose backward kernel also takes the momentum step: a
+// step is two launches (of about 5 us each) instead of four.
+static bool head_steps_itself(const TrainJob& j) {
+  return j.lowest == 5 && j.net->hidden == 0 && head_backward_fused(j.net->n_classes, 512);
+}
+
 // Loss of the batch (labels through fid, loss / correct / flag into ce) and
 // backward of stages 5..lowest; gradients land in j.grad.
 static hipError_t train_backward(TrainJob& j, int nb, const int32_t* fid, float* ce) {
   const Net& net = *j.net;
   const int dt = j.dt;
   hipStream_t st = j.st;
-  const float* f = (j.lowest == 5) ? reinterpret_cast<const float*>(j.x0) : j.pooled;
+  const float* f = (j.lowest == 5) ? j.feat : j.pooled;
   void* dout = j.g[1];
   void* dnext = j.g[2];
   void* gG = j.g[3];
@@ -809,6 +872,8 @@ static hipError_t train_backward(TrainJob& j, int nb, const int32_t* fid, float*
     // softmax cross-entropy, classifier gradients and average-pool backward
     // (with the backward partials of the last block's output BatchNorm)
     HeadBnSink hb;
+    const HeadSgd step{j.master + net.fc_w, j.mom + net.fc_w, j.master + net.fc_b,
+                       j.mom + net.fc_b, j.lr, j.mu};
     if (j.lowest < 5) {
       const size_t lb = net.blk.size() - 1;
       hb.ymask = j.acts[lb].OUT;
@@ -818,7 +883,8 @@ static hipError_t train_backward(TrainJob& j, int nb, const int32_t* fid, float*
     }
     EKYA_HIP(head_backward(dt, j.logits, j.labels, fid, nb, net.n_classes, f, j.master + net.fc_w,
                            512, j.grad + net.fc_w, j.grad + net.fc_b,
-                           j.lowest == 5 ? nullptr : dout, hw, ce, st, &hb));
+                           j.lowest == 5 ? nullptr : dout, hw, ce, st, &hb,
+                           head_steps_itself(j) ? &step : nullptr));
     head_ready = hb.rows;
   } else {
     EKYA_HIP(softmax_ce(j.logits, j.labels, fid, nb, net.n_classes, j.dz, ce, st));
@@ -882,7 +948,7 @@ static hipError_t train_backward(TrainJob& j, int nb, const int32_t* fid, float*
   auto fork = [&]() -> hipError_t {
     if (two) {
       if (nf >= TrainJob::kForks / 2) return hipErrorInvalidValue;
-      EKYA_HIP(hipEventRecord(j.fork[nf], st));
+      EKYA_HIP(record(j, j.fork[nf], st));
       EKYA_HIP(hipStreamWaitEvent(j.st2, j.fork[nf], 0));
       ++nf;
     }
@@ -920,7 +986,7 @@ static hipError_t train_backward(TrainJob& j, int nb, const int32_t* fid, float*
   auto join = [&](int parity) -> hipError_t {  // st2 has queued every reader of this parity
     if (!two) return hipSuccess;
     if (nj >= TrainJob::kForks / 2) return hipErrorInvalidValue;
-    EKYA_HIP(hipEventRecord(j.joined[nj], j.st2));
+    EKYA_HIP(record(j, j.joined[nj], j.st2));
     last_join[parity] = nj++;
     return hipSuccess;
   };
@@ -1052,7 +1118,7 @@ static hipError_t train_backward(TrainJob& j, int nb, const int32_t* fid, float*
   // convolution weights or buffers st2 read.
   if (two) {
     if (nj >= TrainJob::kForks / 2) return hipErrorInvalidValue;
-    EKYA_HIP(hipEventRecord(j.joined[nj], j.st2));
+    EKYA_HIP(record(j, j.joined[nj], j.st2));
     if (deferred >= 0 || st2_grad)
       EKYA_HIP(hipStreamWaitEvent(st, j.joined[nj], 0));
     else
@@ -1103,10 +1169,9 @@ static hipError_t build_cache(const Net& net, const Geo& g, const void* shadow, 
 static hipError_t job_setup(TrainJob& j) {
   const Net& net = *j.net;
   const Tables& t = *j.tabs;
-  EKYA_HIP(weights_to_internal(j.dt, j.weights, j.master, j.master, t.layout, t.n_layout, kMaxTaps,
-                               j.shadow, j.st));
-  EKYA_HIP(pack_crsk(j.dt, j.weights, t.layout_train[j.lowest], t.n_layout_train[j.lowest], j.shadow,
-                     j.st));
+  EKYA_HIP(weights_to_internal(j.dt, j.weights, j.master, j.master, t.layout, j.shadow,
+                               j.st));
+  EKYA_HIP(pack_crsk(j.dt, j.weights, t.layout_train[j.lowest], j.shadow, j.st));
   EKYA_HIP(hipMemsetAsync(j.grad, 0, net.total * sizeof(float), j.st));
   EKYA_HIP(hipMemsetAsync(j.mom, 0, net.total * sizeof(float), j.st));
   EKYA_HIP(hipMemsetAsync(j.hcount, 0, j.epochs * sizeof(int32_t), j.st));
@@ -1127,6 +1192,8 @@ static hipError_t job_epochs(TrainJob& j) {
   int step = 0;
   EKYA_HIP(hipEventRecord(j.ev[0], j.st));
   for (int e = 0; e < j.epochs; ++e) {
+    if (j.lowest == 5)  // 2 KB a row: the epoch's features in one launch
+      EKYA_HIP(gather_rows(j.cache, j.d_order + (size_t)e * j.n_s, j.n_s, j.row_bytes, j.x0, j.st));
     for (int b0 = 0; b0 < j.n_s; b0 += j.B) {
       const int nb = std::min(j.B, j.n_s - b0);
       const int32_t* ord = j.d_order + (size_t)e * j.n_s + b0;
@@ -1135,10 +1202,14 @@ static hipError_t job_epochs(TrainJob& j) {
       if (j.lowest == 0)
         EKYA_HIP(frames_to_padded(j.dt, j.frames, fid, nb, j.geo.H, j.geo.W, net.conv[0].cin_pad,
                                   j.x0, j.st));
+      else if (j.lowest == 5)
+        j.feat = reinterpret_cast<const float*>(j.x0) + (size_t)b0 * 512;
       else
         EKYA_HIP(gather_rows(j.cache, ord, nb, j.row_bytes, j.x0, j.st));
       EKYA_HIP(train_forward(j, nb));
       EKYA_HIP(train_backward(j, nb, fid, j.ce_out + 3 * step));
+      ++step;
+      if (head_steps_itself(j)) continue;
       // the parameters without a fused update (BatchNorm, classifier, and
       // convolutions outside conv_weight_update's reach)
       EKYA_HIP(sgd_momentum_ranges(j.master, j.mom, j.grad, t.sgd_rest[j.lowest],
@@ -1146,7 +1217,6 @@ static hipError_t job_epochs(TrainJob& j) {
                                    j.st));
       EKYA_HIP(pack_conv_weights(j.dt, j.master, t.pack_rest[j.lowest], t.n_pack_rest[j.lowest],
                                  j.shadow, j.st));
-      ++step;
     }
     EKYA_HIP(settle(j));
     EKYA_HIP(hipEventRecord(j.ev_tr[e], j.st));
@@ -1248,47 +1318,23 @@ static hipError_t job_collect(TrainJob& j, JobResult& r) {
   return hipSuccess;
 }
 
-// Every event here orders work between streams of this device (or times it);
-// the host reads results only after a stream synchronisation.  Without the
-// system-scope fence a recorded event costs its stream a shorter bubble.
 static hipError_t create_events(TrainJob& j) {
-  for (int e = 0; e <= j.epochs; ++e)
-    EKYA_HIP(hipEventCreateWithFlags(&j.ev[e], hipEventDisableSystemFence));
-  for (int e = 0; e < j.epochs; ++e) {
-    EKYA_HIP(hipEventCreateWithFlags(&j.ev_tr[e], hipEventDisableSystemFence));
-    EKYA_HIP(hipEventCreateWithFlags(&j.ev_e0[e], hipEventDisableSystemFence));
-    EKYA_HIP(hipEventCreateWithFlags(&j.ev_e1[e], hipEventDisableSystemFence));
-  }
-  if (j.st3) {
-    EKYA_HIP(hipEventCreateWithFlags(&j.ev_eval_fork, hipEventDisableTiming | hipEventDisableSystemFence));
-    EKYA_HIP(hipEventCreateWithFlags(&j.ev_eval_done, hipEventDisableTiming | hipEventDisableSystemFence));
-  }
-  for (int i = 0; i < TrainJob::kForks; ++i) {
-    EKYA_HIP(hipEventCreateWithFlags(&j.fork[i], hipEventDisableTiming | hipEventDisableSystemFence));
-    EKYA_HIP(
-        hipEventCreateWithFlags(&j.joined[i], hipEventDisableTiming | hipEventDisableSystemFence));
-  }
+  for (int e = 0; e <= j.epochs; ++e) EKYA_HIP(j.pool->take(true, &j.ev[e]));
+  for (int e = 0; e < j.epochs; ++e)
+    for (hipEvent_t* a : {j.ev_tr, j.ev_e0, j.ev_e1}) EKYA_HIP(j.pool->take(true, &a[e]));
+  if (j.st3)
+    for (hipEvent_t* e : {&j.ev_eval_fork, &j.ev_eval_done}) EKYA_HIP(j.pool->take(false, e));
   return hipSuccess;
 }
-static void destroy_events(TrainJob& j) {
-  if (j.ev_eval_fork) (void)hipEventDestroy(j.ev_eval_fork);
-  if (j.ev_eval_done) (void)hipEventDestroy(j.ev_eval_done);
-  j.ev_eval_fork = j.ev_eval_done = nullptr;
-  for (int e = 0; e <= EKYA_MAX_EPOCHS; ++e)
-    if (j.ev[e]) {
-      (void)hipEventDestroy(j.ev[e]);
-      j.ev[e] = nullptr;
-    }
+static void release_events(TrainJob& j) {
+  j.pool->give(false, j.ev_eval_fork);
+  j.pool->give(false, j.ev_eval_done);
+  for (hipEvent_t& e : j.ev) j.pool->give(true, e);
   for (hipEvent_t* a : {j.ev_tr, j.ev_e0, j.ev_e1})
-    for (int e = 0; e < EKYA_MAX_EPOCHS; ++e)
-      if (a[e]) {
-        (void)hipEventDestroy(a[e]);
-        a[e] = nullptr;
-      }
+    for (int e = 0; e < EKYA_MAX_EPOCHS; ++e) j.pool->give(true, a[e]);
   for (int i = 0; i < TrainJob::kForks; ++i) {
-    if (j.fork[i]) (void)hipEventDestroy(j.fork[i]);
-    if (j.joined[i]) (void)hipEventDestroy(j.joined[i]);
-    j.fork[i] = j.joined[i] = nullptr;
+    j.pool->give(false, j.fork[i]);
+    j.pool->give(false, j.joined[i]);
   }
 }
 
@@ -1356,7 +1402,8 @@ size_t retrain_workspace_bytes(const Net& net, int k, int n_frames, int H, int W
   TrainJob j;
   config_retrain(j, net, k, n_frames, H, W, n_heldout, o, true);
   RetrainBufs r;
-  Arena a;
+  PlanMemo memo;
+  Arena a(memo);
   plan_retrain(a, j, r);
   return a.used;
 }
@@ -1375,7 +1422,7 @@ ekya_status run_retrain(Ctx& c, float* weights, int k, const void* frames, const
   config_retrain(j, net, k, n_frames, H, W, n_heldout, o, !c.timing);
   RetrainBufs rb;
   {
-    Arena meas;
+    Arena meas(c.memo);
     plan_retrain(meas, j, rb);
     if (ekya_status s = acquire_workspace(c, meas.used, stream)) return s;
   }
@@ -1401,7 +1448,7 @@ ekya_status run_retrain(Ctx& c, float* weights, int k, const void* frames, const
   j.hlabels = hlabels;
   std::vector<int32_t> S = training_subset(n_frames, o.subsample_frac, o.seed);
   job_prepare_host(j, S, o.seed);
-  Arena real;
+  Arena real(c.memo);
   real.base = reinterpret_cast<char*>(c.ws.p);
   plan_retrain(real, j, rb);
   void* cache = rb.cache;
@@ -1412,11 +1459,12 @@ ekya_status run_retrain(Ctx& c, float* weights, int k, const void* frames, const
   j.cache = cache;
   j.hcache = cache ? reinterpret_cast<char*>(cache) + (long long)j.n_s * j.row_bytes : nullptr;
 
-  EKYA_CHECK_HIP(create_events(j));
+  j.pool = &c.events;
   hipEvent_t p0 = nullptr, p1 = nullptr;
-  EKYA_CHECK_HIP(hipEventCreateWithFlags(&p0, hipEventDisableSystemFence));
-  EKYA_CHECK_HIP(hipEventCreateWithFlags(&p1, hipEventDisableSystemFence));
   auto run = [&]() -> hipError_t {
+    EKYA_HIP(create_events(j));
+    EKYA_HIP(c.events.take(true, &p0));
+    EKYA_HIP(c.events.take(true, &p1));
     EKYA_HIP(job_setup(j));
     EKYA_HIP(hipEventRecord(p0, stream));
     if (j.lowest >= 1) {
@@ -1430,8 +1478,7 @@ ekya_status run_retrain(Ctx& c, float* weights, int k, const void* frames, const
     EKYA_HIP(hipEventRecord(p1, stream));
     EKYA_HIP(job_epochs(j));
     // write back: internal -> canonical (frozen parts round-trip exactly)
-    EKYA_HIP(weights_to_canonical(j.master, weights, c.tabs[dt].layout, c.tabs[dt].n_layout,
-                                  kMaxTaps, stream));
+    EKYA_HIP(weights_to_canonical(j.master, weights, c.tabs[dt].layout, stream));
     return hipSuccess;
   };
   hipError_t he = run();
@@ -1440,9 +1487,9 @@ ekya_status run_retrain(Ctx& c, float* weights, int k, const void* frames, const
   if (he == hipSuccess) he = job_collect(j, r);
   float pms = 0.f;
   if (he == hipSuccess) he = hipEventElapsedTime(&pms, p0, p1);
-  destroy_events(j);
-  (void)hipEventDestroy(p0);
-  (void)hipEventDestroy(p1);
+  release_events(j);
+  c.events.give(true, p0);
+  c.events.give(true, p1);
   EKYA_CHECK_HIP(he);
 
   res->n_train = j.n_s;
@@ -1545,7 +1592,8 @@ size_t profile_workspace_bytes(const Net& net, const ekya_profile_cfg* cfgs, int
                                int n_frames, int H, int W, int n_heldout) {
   ProfilePlan pp;
   config_profile(pp, net, cfgs, n_cfgs, n_frames, H, W, n_heldout);
-  Arena a;
+  PlanMemo memo;
+  Arena a(memo);
   plan_profile(a, pp, n_heldout, H, W);
   return a.used;
 }
@@ -1569,7 +1617,7 @@ ekya_status run_profile(Ctx& c, const float* weights, const ekya_profile_cfg* cf
   }
   hipStream_t s0 = c.streams[n_cfgs];
   {
-    Arena meas;
+    Arena meas(c.memo);
     plan_profile(meas, pp, n_heldout, H, W);
     if (ekya_status s = acquire_workspace(c, meas.used, s0)) return s;
   }
@@ -1581,6 +1629,7 @@ ekya_status run_profile(Ctx& c, const float* weights, const ekya_profile_cfg* cf
   for (int i = 0; i < n_cfgs; ++i) {
     TrainJob& j = jobs[i];
     j.tabs = &c.tabs[dt];
+    j.pool = &c.events;
     j.st = c.streams[i];
     j.st2 = c.timing ? j.st : c.streams[n_cfgs + 1 + i];
     j.weights = weights;
@@ -1592,7 +1641,7 @@ ekya_status run_profile(Ctx& c, const float* weights, const ekya_profile_cfg* cf
     job_prepare_host(j, Si, cfgs[i].shuffle_seed);
   }
   const int ccap = kCacheChunk;
-  Arena real;
+  Arena real(c.memo);
   real.base = reinterpret_cast<char*>(c.ws.p);
   plan_profile(real, pp, n_heldout, H, W);
   int32_t* d_S = pp.d_S;
@@ -1605,8 +1654,7 @@ ekya_status run_profile(Ctx& c, const float* weights, const ekya_profile_cfg* cf
   // caches: the frozen prefix of the starting weights, built once per depth on s0
   const Tables& t = c.tabs[dt];
   auto build = [&]() -> hipError_t {
-    EKYA_HIP(weights_to_internal(dt, weights, nullptr, pmaster, t.layout, t.n_layout, kMaxTaps,
-                                 pshadow, s0));
+    EKYA_HIP(weights_to_internal(dt, weights, nullptr, pmaster, t.layout, pshadow, s0));
     EKYA_HIP(bn_fold(pmaster, t.fold_all, t.n_fold_all, pfold, s0));
     if (!caches.empty())
       EKYA_HIP(hipMemcpyAsync(d_S, S.data(), S.size() * sizeof(int32_t), hipMemcpyHostToDevice, s0));
@@ -1683,7 +1731,7 @@ ekya_status run_profile(Ctx& c, const float* weights, const ekya_profile_cfg* cf
         c.err = "training loss is not finite";
       }
     }
-    destroy_events(j);
+    release_events(j);
   }
   // every candidate's streams are idle before the next call reuses the arena
   for (const TrainJob& j : jobs) {
@@ -1720,7 +1768,8 @@ static void plan_infer(Arena& a, const Net& net, const Geo& geo, int resolution,
 
 size_t infer_workspace_bytes(const Net& net, int resolution) {
   InferBufs b;
-  Arena a;
+  PlanMemo memo;
+  Arena a(memo);
   plan_infer(a, net, Geo::build(net, resolution, resolution), resolution, b);
   return a.used;
 }
@@ -1772,17 +1821,16 @@ ekya_status run_infer(Ctx& c, const float* weights, const void* frames, int n, i
   const Geo geo = Geo::build(net, resolution, resolution);
   InferBufs ib;
   {
-    Arena meas;
+    Arena meas(c.memo);
     plan_infer(meas, net, geo, resolution, ib);
     if (ekya_status s = acquire_workspace(c, meas.used, stream)) return s;
   }
-  Arena real;
+  Arena real(c.memo);
   real.base = reinterpret_cast<char*>(c.ws.p);
   plan_infer(real, net, geo, resolution, ib);
   const Tables& t = c.tabs[dt];
   auto run = [&]() -> hipError_t {
-    EKYA_HIP(weights_to_internal(dt, weights, nullptr, ib.master, t.layout, t.n_layout, kMaxTaps,
-                                 ib.shadow, stream));
+    EKYA_HIP(weights_to_internal(dt, weights, nullptr, ib.master, t.layout, ib.shadow, stream));
     EKYA_HIP(bn_fold(ib.master, t.fold_all, t.n_fold_all, ib.fold, stream));
     return infer_frames(net, geo, ib.master, ib.fold, ib.shadow, frames, n, H, W, resolution,
                         labels_out, ib, stream);
@@ -1802,14 +1850,15 @@ hipError_t model_init(Model& m, int device, int n_classes, int hidden, int dt) {
   EKYA_HIP(hipSetDevice(device));
   m.net = Net::build(n_classes, dt, hidden);
   EKYA_HIP(upload_tables(m.net, m.tabs));
-  Arena a;
+  PlanMemo none;
+  Arena a(none);
   for (int i = 0; i < 2; ++i) {
     a.take<float>(m.net.total);
     a.take<float>(2 * m.net.bn_channels);
     a.take_bytes(m.net.shadow_elems * dtype_size(dt));
   }
   EKYA_HIP(m.mem.alloc(a.used));
-  Arena r;
+  Arena r(none);
   r.base = reinterpret_cast<char*>(m.mem.p);
   for (ModelSlot& sl : m.slot) {
     sl.master = r.take<float>(m.net.total);
@@ -1865,8 +1914,8 @@ hipError_t model_load(Model& m, const float* canonical, const float* internal, h
   for (auto& u : sl.uses) m.pool.push_back(u.second);
   sl.uses.clear();
   if (canonical) {
-    EKYA_HIP(weights_to_internal(m.dt, canonical, sl.master, sl.master, m.tabs.layout,
-                                 m.tabs.n_layout, kMaxTaps, sl.shadow, stream));
+    EKYA_HIP(weights_to_internal(m.dt, canonical, sl.master, sl.master, m.tabs.layout, sl.shadow,
+                                 stream));
   } else {
     EKYA_HIP(hipMemcpyAsync(sl.master, internal, m.net.total * sizeof(float),
                             hipMemcpyDeviceToDevice, stream));
@@ -1889,8 +1938,7 @@ hipError_t model_export(Model& m, float* canonical_out, hipStream_t stream, uint
   EKYA_HIP(hipSetDevice(m.device));
   ModelSlot& sl = m.slot[m.current];
   EKYA_HIP(hipStreamWaitEvent(stream, sl.ready, 0));
-  EKYA_HIP(weights_to_canonical(sl.master, canonical_out, m.tabs.layout, m.tabs.n_layout, kMaxTaps,
-                                stream));
+  EKYA_HIP(weights_to_canonical(sl.master, canonical_out, m.tabs.layout, stream));
   EKYA_HIP(model_note_use(m, m.current, stream));
   if (version) *version = sl.version;
   return hipSuccess;
@@ -1909,7 +1957,8 @@ static int infer_lanes(int n_models) { return std::max(1, std::min(n_models, kIn
 
 size_t infer_models_workspace_bytes(const Net& net, int resolution, int n_models) {
   InferBufs b;
-  Arena a;
+  PlanMemo memo;
+  Arena a(memo);
   const Geo g = Geo::build(net, resolution, resolution);
   for (int l = 0; l < infer_lanes(n_models); ++l) plan_infer(a, net, g, resolution, b, false);
   return a.used;
@@ -1925,7 +1974,7 @@ ekya_status run_infer_models(Ctx& c, Model* const* models, int n_models, const v
   const Geo geo = Geo::build(net, resolution, resolution);
   const int lanes = infer_lanes(n_models);
   {
-    Arena meas;
+    Arena meas(c.memo);
     InferBufs b;
     for (int l = 0; l < lanes; ++l) plan_infer(meas, net, geo, resolution, b, false);
     if (ekya_status s = acquire_workspace(c, meas.used, stream)) return s;
@@ -1940,7 +1989,7 @@ ekya_status run_infer_models(Ctx& c, Model* const* models, int n_models, const v
     for (int l = 0; l < kInferLanes; ++l)
       EKYA_CHECK_HIP(hipEventCreateWithFlags(&c.lane_join[l], hipEventDisableTiming));
   }
-  Arena real;
+  Arena real(c.memo);
   real.base = reinterpret_cast<char*>(c.ws.p);
   std::vector<InferBufs> ib(lanes);
   for (int l = 0; l < lanes; ++l) plan_infer(real, net, geo, resolution, ib[l], false);
@@ -1986,11 +2035,11 @@ ekya_status run_infer_model(Ctx& c, Model& m, const void* frames, int n, int H, 
   const Geo geo = Geo::build(net, resolution, resolution);
   InferBufs ib;
   {
-    Arena meas;
+    Arena meas(c.memo);
     plan_infer(meas, net, geo, resolution, ib, false);
     if (ekya_status s = acquire_workspace(c, meas.used, stream)) return s;
   }
-  Arena real;
+  Arena real(c.memo);
   real.base = reinterpret_cast<char*>(c.ws.p);
   plan_infer(real, net, geo, resolution, ib, false);
   hipError_t he;

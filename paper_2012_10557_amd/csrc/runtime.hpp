@@ -2,6 +2,7 @@
 // retraining / profiling / inference jobs.
 #pragma once
 
+#include <array>
 #include <map>
 #include <mutex>
 #include <string>
@@ -22,10 +23,39 @@ struct DeviceBuf {
   void release();
 };
 
+// Scratch sizes already worked out, by what they depend on: the kind of
+// scratch, precision, frame size, stages and frame count.  The size of split
+// scratch is a maximum over every convolution and every frame count up to a
+// batch or chunk (about 10,000 plans, 0.1 ms per planning pass for
+// inference and 0.5 ms for full-depth retraining, several times per call).
+struct PlanMemo {
+  static constexpr size_t kMost = 512;
+  std::map<std::array<int, 7>, size_t> size;
+  template <typename F> size_t get(const std::array<int, 7>& key, F&& f) {
+    auto it = size.find(key);
+    if (it != size.end()) return it->second;
+    if (size.size() >= kMost) size.clear();
+    return size[key] = f();
+  }
+};
+
+// Events kept between a context's calls (creating and destroying a
+// retraining job's took about 0.2 ms per call).  Candidates of one profiling
+// call take theirs from several threads.
+struct EventPool {
+  std::mutex mu;
+  std::vector<hipEvent_t> timed, plain;
+  hipError_t take(bool timing, hipEvent_t* e);
+  void give(bool timing, hipEvent_t& e);  // e null: nothing to give back
+  void release();
+};
+
 // Bump allocator over a DeviceBuf; a measuring pass (base == nullptr) sizes it.
 struct Arena {
+  PlanMemo* memo;
   char* base = nullptr;
   size_t used = 0;
+  explicit Arena(PlanMemo& m) : memo(&m) {}
   template <typename T> T* take(size_t count) {
     size_t a = (used + 255) & ~(size_t)255;
     used = a + count * sizeof(T);
@@ -37,8 +67,7 @@ struct Arena {
 // Device copies of the per-network tables the kernels read.
 struct Tables {
   DeviceBuf buf;
-  const long long* layout = nullptr;  // every tensor
-  int n_layout = 0;
+  LayoutTable layout;  // every tensor
   const long long* fold_all = nullptr;
   int n_fold_all = 0;
   const long long* pack_all = nullptr;  // every conv, [K][R][S][C] shadow only
@@ -46,8 +75,7 @@ struct Tables {
   // per lowest trainable stage (0..5)
   const long long* fold_train[6] = {nullptr};
   int n_fold_train[6] = {0};
-  const long long* layout_train[6] = {nullptr};  // the rows of `layout` from that stage on
-  int n_layout_train[6] = {0};
+  LayoutTable layout_train[6];  // the rows of `layout` from that stage on
   // step-end SGD ranges (offset, length) and repacking of the parameters
   // without a fused per-convolution update
   const long long* sgd_rest[6] = {nullptr};
@@ -123,6 +151,8 @@ struct Ctx {
   // previous call has finished.
   DeviceBuf ws;
   bool fixed_ws = false;
+  PlanMemo memo;
+  EventPool events;
   // Recorded after the last work of every call that used the arena; the next
   // call's stream waits for it (calls on one context run in turn on the GPU).
   hipEvent_t last_done = nullptr;

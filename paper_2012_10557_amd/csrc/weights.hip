@@ -19,7 +19,11 @@ namespace {
 
 constexpr int ROW_MAX = 4608;   // floats of a row (or part of one) staged in LDS
 constexpr int CRSK_MAX = 128;   // floats of an output channel per transposing tile
-constexpr int LAYOUT_COLS = 7;  // off, K, C, RS, Cp, krsc offset, crsk offset
+
+// The table row a block works on: row blockIdx.y of tab, or `one`.
+__device__ __forceinline__ LayoutRow layout_row(const LayoutRow* tab, const LayoutRow& one) {
+  return tab ? tab[blockIdx.y] : one;
+}
 
 template <typename T> __device__ __forceinline__ T low(float v) { return (T)v; }
 
@@ -29,17 +33,18 @@ template <typename T> __device__ __forceinline__ T low(float v) { return (T)v; }
 // Otherwise src master, dst canonical.
 template <typename T, bool TO_INTERNAL>
 __global__ __launch_bounds__(256) void layout_kernel(const float* src, float* dst, float* rest,
-                                                     const long long* tab, T* shadow) {
+                                                     const LayoutRow* tab, LayoutRow one,
+                                                     T* shadow) {
   __shared__ float buf[ROW_MAX];
-  const long long* row = tab + LAYOUT_COLS * blockIdx.y;
-  const long long off = row[0];
-  const int C = (int)row[2], RS = (int)row[3], Cp = (int)row[4], t = threadIdx.x;
-  const bool packed = TO_INTERNAL && shadow && row[5] >= 0;
+  const LayoutRow row = layout_row(tab, one);
+  const long long off = row.off;
+  const int C = (int)row.C, RS = (int)row.RS, Cp = (int)row.Cp, t = threadIdx.x;
+  const bool packed = TO_INTERNAL && shadow && row.krsc >= 0;
   if constexpr (TO_INTERNAL)
-    if (row[5] < 0) dst = rest;
+    if (row.krsc < 0) dst = rest;
   // (host: RS <= ROW_MAX, so rs * C + c below stays under 2^31)
   if (RS == 1 && (!packed || Cp == C)) {  // same order: a straight copy
-    const long long n = row[1] * C;
+    const long long n = row.K * C;
     for (long long i = blockIdx.x * 1024LL + t; i < n; i += gridDim.x * 1024LL) {
       float v[4];
 #pragma unroll
@@ -48,14 +53,14 @@ __global__ __launch_bounds__(256) void layout_kernel(const float* src, float* ds
       for (int j = 0; j < 4; ++j)
         if (i + 256 * j < n) {
           if (dst) dst[off + i + 256 * j] = v[j];
-          if (packed) shadow[row[5] + i + 256 * j] = low<T>(v[j]);
+          if (packed) shadow[row.krsc + i + 256 * j] = low<T>(v[j]);
         }
     }
     return;
   }
   const int part = min(C, ROW_MAX / RS);  // channels per staged part (host: RS <= ROW_MAX)
   const int parts = cdiv(C, part);
-  const long long items = row[1] * parts;
+  const long long items = row.K * parts;
   for (long long it = blockIdx.x; it < items; it += gridDim.x) {
     const long long k = it / parts;
     const int c0 = (int)(it % parts) * part, cn = min(part, C - c0), n = cn * RS;
@@ -74,7 +79,7 @@ __global__ __launch_bounds__(256) void layout_kernel(const float* src, float* ds
           if (i0 + 256 * j < n) buf[i0 + 256 * j] = v[j];
       }
       __syncthreads();
-      T* low_row = packed ? shadow + row[5] + k * RS * Cp + c0 : nullptr;
+      T* low_row = packed ? shadow + row.krsc + k * RS * Cp + c0 : nullptr;
       for (int i0 = t; i0 < n; i0 += 256 * 9) {
         float v[9];
         int at[9], al[9];
@@ -104,7 +109,7 @@ __global__ __launch_bounds__(256) void layout_kernel(const float* src, float* ds
       }
       if (packed && c0 + cn == C)  // channels padded to the 16-byte unit
         for (int i = t; i < RS * (Cp - C); i += 256)
-          shadow[row[5] + (k * RS + i / (Cp - C)) * Cp + C + i % (Cp - C)] = low<T>(0.f);
+          shadow[row.krsc + (k * RS + i / (Cp - C)) * Cp + C + i % (Cp - C)] = low<T>(0.f);
     } else {
       for (int i0 = t; i0 < n; i0 += 256 * 9) {
         float v[9];
@@ -135,16 +140,16 @@ __global__ __launch_bounds__(256) void layout_kernel(const float* src, float* ds
 // Filters of more than ROW_MAX taps: element by element.
 template <typename T>
 __global__ __launch_bounds__(256) void layout_any_kernel(const float* src, float* dst,
-                                                         const long long* tab, T* shadow,
-                                                         int to_internal) {
-  const long long* row = tab + LAYOUT_COLS * blockIdx.y;
-  const long long off = row[0], C = row[2], RS = row[3], Cp = row[4], n = row[1] * RS * Cp;
+                                                         const LayoutRow* tab, LayoutRow one,
+                                                         T* shadow, int to_internal) {
+  const LayoutRow row = layout_row(tab, one);
+  const long long off = row.off, C = row.C, RS = row.RS, Cp = row.Cp, n = row.K * RS * Cp;
   for (long long i = blockIdx.x * 256LL + threadIdx.x; i < n; i += gridDim.x * 256LL) {
     const long long c = i % Cp, rs = i / Cp % RS, k = i / (Cp * RS);  // [k][rs][padded c]
     const long long a = off + (k * C + c) * RS + rs, b = off + (k * RS + rs) * C + c;
     const float v = c < C ? src[to_internal ? a : b] : 0.f;
     if (c < C && dst) dst[to_internal ? b : a] = v;
-    if (shadow && row[5] >= 0) shadow[row[5] + i] = low<T>(v);
+    if (shadow && row.krsc >= 0) shadow[row.krsc + i] = low<T>(v);
   }
 }
 
@@ -152,19 +157,19 @@ __global__ __launch_bounds__(256) void layout_any_kernel(const float* src, float
 // channels x `part` input channels, read in runs of part * RS floats and
 // written in runs of 64 elements.
 template <typename T>
-__global__ __launch_bounds__(256) void pack_crsk_kernel(const float* src, const long long* tab,
-                                                        T* shadow) {
+__global__ __launch_bounds__(256) void pack_crsk_kernel(const float* src, const LayoutRow* tab,
+                                                        LayoutRow one, T* shadow) {
   __shared__ float tile[64][CRSK_MAX + 1];
-  const long long* row = tab + LAYOUT_COLS * blockIdx.y;
-  if (row[6] < 0) return;
-  const int K = (int)row[1], C = (int)row[2], RS = (int)row[3], t = threadIdx.x;
+  const LayoutRow row = layout_row(tab, one);
+  if (row.crsk < 0) return;
+  const int K = (int)row.K, C = (int)row.C, RS = (int)row.RS, t = threadIdx.x;
   const int part = max(1, 72 / RS);  // 8 channels x 9 taps (host: RS <= CRSK_MAX)
   const int tk = cdiv(K, 64), tc = cdiv(C, part);
   const int kk = t & 63, w = t >> 6;
   for (long long it = blockIdx.x; it < (long long)tk * tc; it += gridDim.x) {
     const int k0 = (int)(it / tc) * 64, c0 = (int)(it % tc) * part;
     const int n = min(part, C - c0) * RS, kn = min(64, K - k0);
-    const float* from = src + row[0] + ((long long)k0 * C + c0) * RS;
+    const float* from = src + row.off + ((long long)k0 * C + c0) * RS;
     int r = t / n, e = t - r * n;
     const int dr = 256 / n, de = 256 - dr * n;
     for (int i0 = t; i0 < kn * n; i0 += 256 * 9) {
@@ -188,7 +193,7 @@ __global__ __launch_bounds__(256) void pack_crsk_kernel(const float* src, const 
     }
     __syncthreads();
     if (kk < kn) {
-      T* to = shadow + row[6] + (long long)c0 * RS * K + k0 + kk;
+      T* to = shadow + row.crsk + (long long)c0 * RS * K + k0 + kk;
 #pragma unroll 6
       for (int u = w; u < n; u += 4)  // u: (channel, tap)
         to[(long long)u * K] = low<T>(tile[kk][u]);
@@ -208,41 +213,41 @@ constexpr int LAYOUT_BLOCKS = 256;
 }  // namespace
 
 hipError_t weights_to_internal(int dt, const float* canonical, float* master, float* rest,
-                               const long long* tab, int n, int max_taps, void* shadow,
-                               hipStream_t stream) {
-  if (n == 0) return hipSuccess;
+                               const LayoutTable& tab, void* shadow, hipStream_t stream) {
+  if (tab.n == 0) return hipSuccess;
   return with_type(dt, [&](auto* tp) {
     using T = std::remove_pointer_t<decltype(tp)>;
-    if (max_taps > ROW_MAX)
-      hipLaunchKernelGGL(layout_any_kernel<T>, dim3(1024, n), dim3(256), 0, stream, canonical,
-                         master, tab, (T*)shadow, 1);
+    if (tab.max_taps > ROW_MAX)
+      hipLaunchKernelGGL(layout_any_kernel<T>, dim3(1024, tab.n), dim3(256), 0, stream, canonical,
+                         master, tab.rows, tab.one, (T*)shadow, 1);
     else
-      hipLaunchKernelGGL((layout_kernel<T, true>), dim3(LAYOUT_BLOCKS, n), dim3(256), 0, stream,
-                         canonical, master, rest, tab, (T*)shadow);
+      hipLaunchKernelGGL((layout_kernel<T, true>), dim3(LAYOUT_BLOCKS, tab.n), dim3(256), 0, stream,
+                         canonical, master, rest, tab.rows, tab.one, (T*)shadow);
   });
 }
 
-hipError_t weights_to_canonical(const float* master, float* canonical, const long long* tab, int n,
-                                int max_taps, hipStream_t stream) {
-  if (n == 0) return hipSuccess;
-  if (max_taps > ROW_MAX)
-    hipLaunchKernelGGL(layout_any_kernel<float>, dim3(1024, n), dim3(256), 0, stream, master,
-                       canonical, tab, (float*)nullptr, 0);
+hipError_t weights_to_canonical(const float* master, float* canonical, const LayoutTable& tab,
+                                hipStream_t stream) {
+  if (tab.n == 0) return hipSuccess;
+  if (tab.max_taps > ROW_MAX)
+    hipLaunchKernelGGL(layout_any_kernel<float>, dim3(1024, tab.n), dim3(256), 0, stream, master,
+                       canonical, tab.rows, tab.one, (float*)nullptr, 0);
   else
-    hipLaunchKernelGGL((layout_kernel<float, false>), dim3(LAYOUT_BLOCKS, n), dim3(256), 0, stream,
-                       master, canonical, (float*)nullptr, tab, (float*)nullptr);
+    hipLaunchKernelGGL((layout_kernel<float, false>), dim3(LAYOUT_BLOCKS, tab.n), dim3(256), 0,
+                       stream, master, canonical, (float*)nullptr, tab.rows, tab.one,
+                       (float*)nullptr);
   return hipGetLastError();
 }
 
 bool pack_crsk_ok(int taps) { return taps <= CRSK_MAX; }
 
-hipError_t pack_crsk(int dt, const float* canonical, const long long* tab, int n, void* shadow,
+hipError_t pack_crsk(int dt, const float* canonical, const LayoutTable& tab, void* shadow,
                      hipStream_t stream) {
-  if (n == 0) return hipSuccess;
+  if (tab.n == 0) return hipSuccess;
   return with_type(dt, [&](auto* tp) {
     using T = std::remove_pointer_t<decltype(tp)>;
-    hipLaunchKernelGGL(pack_crsk_kernel<T>, dim3(LAYOUT_BLOCKS, n), dim3(256), 0, stream,
-                       canonical, tab, (T*)shadow);
+    hipLaunchKernelGGL(pack_crsk_kernel<T>, dim3(LAYOUT_BLOCKS, tab.n), dim3(256), 0, stream,
+                       canonical, tab.rows, tab.one, (T*)shadow);
   });
 }
 
