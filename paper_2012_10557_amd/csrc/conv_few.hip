@@ -12,13 +12,16 @@
 // whole 128-byte line; loading the MFMA operands straight into registers, 16
 // rows per instruction, measured a quarter of that rate), and the partial
 // tiles are added in wave order through LDS, where the epilogue (scale, shift,
-// residual, ReLU) also runs.  Blocks of an XCD cover a contiguous range of
+// residual, ReLU) also runs.  In the two larger tiles several waves share a
+// ring (four waves with private rings, one per SIMD, could not overlap their
+// copies, LDS reads and MFMAs: 7.4 against 5.9 us for 128 channels at 28 x 28,
+// 4 frames).  Blocks of an XCD cover a contiguous range of
 // channel tiles, so that its L2 fetches only those rows of the weights.
 // Measured (MI355X, bf16, 224 px, split tiles + reduction before): 512
-// channels at 7 x 7, 4 frames 18.9 -> 7.8 us, 16 frames 22.1 -> 15.0;
-// 256 at 14 x 14, 4 frames 17.2 -> 6.8, 36 frames 33.2 -> 22.4; 128 at
-// 28 x 28, 4 frames 15.2 -> 7.4, 16 frames 22.1 -> 16.7.  fp32: 64 channels at
-// 16 x 16, 48 frames 23.0 -> 17.7 us; 256 at 14 x 14, 16 frames 60.8 -> 48.9.
+// channels at 7 x 7, 4 frames 18.9 -> 7.0 us, 16 frames 22.1 -> 13.6;
+// 256 at 14 x 14, 4 frames 17.2 -> 5.9, 36 frames 33.2 -> 22.3; 128 at
+// 28 x 28, 4 frames 15.2 -> 5.9, 16 frames 22.1 -> 14.0.  fp32: 64 channels at
+// 16 x 16, 48 frames 23.0 -> 15.0 us; 256 at 14 x 14, 16 frames 60.8 -> 48.6.
 #include "kernels.hpp"
 
 namespace ekya {
@@ -48,6 +51,56 @@ struct FewArgs {
   ConvEpilogue epi;
   int tiles_m, tiles_n;
 };
+
+// Sum of the partial tiles in order, then the epilogue.
+template <typename T, int TM, int TN, int PARTS, int THREADS>
+__device__ __forceinline__ void few_epilogue(const FewArgs& a, const float* red, int m0, int n0,
+                                             int npix) {
+  constexpr int PITCH = TM + 4;
+  const ConvGeom& g = a.g;
+  const ConvEpilogue& e = a.epi;
+  for (int o = threadIdx.x; o < TN * (TM / 4); o += THREADS) {
+    const int pl = o / (TM / 4), cl = (o % (TM / 4)) * 4, k = m0 + cl;
+    const long long pix = n0 + pl;
+    if (pix >= npix || k >= g.K) continue;
+    f32x4 s = *reinterpret_cast<const f32x4*>(red + pl * PITCH + cl);
+#pragma unroll
+    for (int w = 1; w < PARTS; ++w)
+      s += *reinterpret_cast<const f32x4*>(red + (w * TN + pl) * PITCH + cl);
+    float v[4] = {s[0], s[1], s[2], s[3]};
+    const long long at = pix * g.K + k;
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      if (e.scale) v[u] *= e.scale[k + u];
+      if (e.shift) v[u] += e.shift[k + u];
+    }
+    if (e.res) {
+      float r[4];
+      load4<T>(reinterpret_cast<const T*>(e.res) + at, r);
+#pragma unroll
+      for (int u = 0; u < 4; ++u) v[u] += r[u];
+    }
+    if (e.relu) {
+#pragma unroll
+      for (int u = 0; u < 4; ++u) v[u] = relu_nan(v[u]);
+    }
+    store4<T>(reinterpret_cast<T*>(a.y) + at, v);
+  }
+}
+
+// Position of output pixel `pix`: its first input row and column (a row that
+// is never inside the image for a pixel past the last), and its element offset
+// in the image at *px.
+template <typename T>
+__device__ __forceinline__ void few_pixel(const ConvGeom& g, int pix, int npix, int* h0, int* w0,
+                                          int* row, const T** px, const T* x) {
+  const int pp = pix < npix ? pix : 0, n = pp / (g.P * g.Q), rem = pp - n * (g.P * g.Q);
+  const int p = rem / g.Q;
+  *h0 = pix < npix ? p * g.stride - g.pad : -(1 << 30);
+  *w0 = (rem - p * g.Q) * g.stride - g.pad;
+  *row = ((p * g.stride - g.pad) * g.W + *w0) * g.C;  // used inside the image only
+  *px = x + (long long)n * g.H * g.W * g.C;
+}
 
 // A stage is 8 units (128 bytes) of every tile row: 64 bf16 or 32 fp32
 // reduction elements, never straddling a filter tap.  NW waves, each with a
@@ -79,13 +132,7 @@ __global__ __launch_bounds__(NW * 64) void conv_few_kernel(FewArgs a) {
     pa[i] = (const T*)a.w + (long long)min(m0 + 8 * i + r8, g.K - 1) * Ktot + unit;
 #pragma unroll
   for (int j = 0; j < CB; ++j) {
-    const int pix = n0 + 8 * j + r8;
-    const int pp = pix < npix ? pix : 0, n = pp / (g.P * g.Q), rem = pp - n * (g.P * g.Q);
-    const int p = rem / g.Q;
-    h0[j] = pix < npix ? p * g.stride - g.pad : -(1 << 30);  // never inside the image
-    w0[j] = (rem - p * g.Q) * g.stride - g.pad;
-    row[j] = ((p * g.stride - g.pad) * g.W + w0[j]) * g.C;  // used inside the image only
-    pb[j] = (const T*)a.x + (long long)n * g.H * g.W * g.C + unit;
+    few_pixel(g, n0 + 8 * j + r8, npix, &h0[j], &w0[j], &row[j], &pb[j], (const T*)a.x + unit);
   }
   int rs = s0 * SE / g.C, tc = s0 * SE - rs * g.C, tr = rs / g.S, ts = rs - tr * g.S;
   const void* zero = g_few_zero;
@@ -155,42 +202,128 @@ __global__ __launch_bounds__(NW * 64) void conv_few_kernel(FewArgs a) {
     for (int j = 0; j < TJ; ++j)
       *reinterpret_cast<f32x4*>(red + (wave * TN + 16 * j + fr) * PITCH + 16 * i + 4 * q) = acc[i][j];
   __syncthreads();
-  const ConvEpilogue& e = a.epi;
-  for (int o = threadIdx.x; o < TN * (TM / 4); o += NW * 64) {
-    const int pl = o / (TM / 4), cl = (o % (TM / 4)) * 4, k = m0 + cl;
-    const long long pix = n0 + pl;
-    if (pix >= npix || k >= g.K) continue;
-    f32x4 s = *reinterpret_cast<const f32x4*>(red + pl * PITCH + cl);
-#pragma unroll
-    for (int w = 1; w < NW; ++w)
-      s += *reinterpret_cast<const f32x4*>(red + (w * TN + pl) * PITCH + cl);
-    float v[4] = {s[0], s[1], s[2], s[3]};
-    const long long at = pix * g.K + k;
-#pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      if (e.scale) v[u] *= e.scale[k + u];
-      if (e.shift) v[u] += e.shift[k + u];
-    }
-    if (e.res) {
-      float r[4];
-      load4<T>(reinterpret_cast<const T*>(e.res) + at, r);
-#pragma unroll
-      for (int u = 0; u < 4; ++u) v[u] += r[u];
-    }
-    if (e.relu) {
-#pragma unroll
-      for (int u = 0; u < 4; ++u) v[u] = relu_nan(v[u]);
-    }
-    store4<T>(reinterpret_cast<T*>(a.y) + at, v);
-  }
+  few_epilogue<T, TM, TN, NW, NW * 64>(a, red, m0, n0, npix);
 }
 
-template <typename T, int TM, int TN, int NW, int NB>
+// The same for the larger tiles, whose operands several waves share: NG groups
+// of waves split the reduction, a group's (TM / 32) (TN / 32) waves each
+// compute a 32 x 32 quadrant of the tile and copy an equal part of the group's
+// stages.  One barrier per stage (all groups), NB - 1 stages in flight.
+template <typename T, int TM, int TN, int NG, int NB>
+__global__ __launch_bounds__(NG * (TM / 32) * (TN / 32) * 64) void conv_few_shared_kernel(
+    FewArgs a) {
+  constexpr int E = Elt<T>::E, SE = 8 * E, WN = TN / 32, WG = (TM / 32) * WN;
+  constexpr int CA = TM / 8 / WG, CB = TN / 8 / WG, CP = CA + CB;  // a wave's copies per stage
+  constexpr int SU = (TM + TN) * 8, PITCH = TM + 4;  // units per stage; floats per partial row
+  constexpr int RING = NG * NB * SU, RED = NG * TN * PITCH / 4;
+  static_assert(CA * WG * 8 == TM && CB * WG * 8 == TN, "whole copies per wave");
+  __shared__ uint4 smem[RING > RED ? RING : RED];
+  const ConvGeom& g = a.g;
+  const int lane = threadIdx.x & 63, fr = lane & 15, q = lane >> 4;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int grp = wave / WG, wl = wave % WG;
+  const int total = a.tiles_m * a.tiles_n, xcd = blockIdx.x & 7;
+  const int item = xcd * (total >> 3) + min(xcd, total & 7) + (blockIdx.x >> 3);
+  const int m0 = (item / a.tiles_n) * TM, n0 = (item % a.tiles_n) * TN;
+  const int npix = g.N * g.P * g.Q, Ktot = g.R * g.S * g.C, ns = Ktot / SE;
+  const int s0 = ns * grp / NG, count = ns * (grp + 1) / NG - s0, rounds = cdiv(ns, NG);
+
+  const int r8 = lane >> 3, unit = ((lane & 7) ^ r8) * E;
+  const T *pa[CA], *pb[CB];
+  int h0[CB], w0[CB], row[CB];
+#pragma unroll
+  for (int i = 0; i < CA; ++i)
+    pa[i] = (const T*)a.w + (long long)min(m0 + 8 * (wl + WG * i) + r8, g.K - 1) * Ktot + unit;
+#pragma unroll
+  for (int j = 0; j < CB; ++j) {
+    few_pixel(g, n0 + 8 * (wl + WG * j) + r8, npix, &h0[j], &w0[j], &row[j], &pb[j],
+              (const T*)a.x + unit);
+  }
+  int rs = s0 * SE / g.C, tc = s0 * SE - rs * g.C, tr = rs / g.S, ts = rs - tr * g.S;
+  const void* zero = g_few_zero;
+  asm volatile("" : "+s"(zero));
+  uint4* ring = smem + grp * (NB * SU);
+  auto issue = [&](int st, uint4* slot) {
+    const int k0 = st * SE, tap = (tr * g.W + ts) * g.C + tc;
+#pragma unroll
+    for (int i = 0; i < CA; ++i) few_copy(pa[i] + k0, slot + (wl + WG * i) * 64);
+#pragma unroll
+    for (int j = 0; j < CB; ++j) {
+      const bool in = (unsigned)(h0[j] + tr) < (unsigned)g.H && (unsigned)(w0[j] + ts) < (unsigned)g.W;
+      few_copy(in ? (const void*)(pb[j] + (row[j] + tap)) : zero, slot + (TM / 8 + wl + WG * j) * 64);
+    }
+    tc += SE;
+    if (tc >= g.C) {
+      tc = 0;
+      if (++ts == g.S) {
+        ts = 0;
+        ++tr;
+      }
+    }
+  };
+
+  const int wm = wl / WN, wn = wl % WN;
+  f32x4 acc[2][2];
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+#pragma unroll
+    for (int j = 0; j < 2; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int p = 0; p < NB - 1; ++p)
+    if (p < count) issue(s0 + p, ring + p * SU);
+  const int off[2] = {fr * 8 + (q ^ (fr & 7)), fr * 8 + ((4 + q) ^ (fr & 7))};
+  int slot = 0;
+  for (int it = 0; it < rounds; ++it) {
+    // the wave's copies of stage `it` have landed (later ones may be in flight)
+    if (it + NB - 2 < count)
+      few_wait<CP * (NB - 2)>();
+    else
+      few_wait<0>();
+    // every wave's copies are visible, and stage it - 1 has been read
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+    if (it + NB - 1 < count) issue(s0 + it + NB - 1, ring + (slot == 0 ? NB - 1 : slot - 1) * SU);
+    if (it < count) {
+      const uint4* As = ring + slot * SU + wm * 256;
+      const uint4* Bs = ring + slot * SU + TM * 8 + wn * 256;
+#pragma unroll
+      for (int kf = 0; kf < 2; ++kf) {
+        uint4 fa[2], fb[2];
+#pragma unroll
+        for (int i = 0; i < 2; ++i) fa[i] = As[i * 128 + off[kf]];
+#pragma unroll
+        for (int j = 0; j < 2; ++j) fb[j] = Bs[j * 128 + off[kf]];
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+#pragma unroll
+          for (int j = 0; j < 2; ++j) mma_unit(acc[i][j], fa[i], fb[j], (T*)nullptr);
+      }
+    }
+    if (++slot == NB) slot = 0;
+  }
+  __syncthreads();
+  float* red = reinterpret_cast<float*>(smem);
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+      *reinterpret_cast<f32x4*>(red + (grp * TN + 32 * wn + 16 * j + fr) * PITCH + 32 * wm + 16 * i +
+                                4 * q) = acc[i][j];
+  __syncthreads();
+  few_epilogue<T, TM, TN, NG, NG * WG * 64>(a, red, m0, n0, npix);
+}
+
+template <typename T, int TM, int TN, int NW, int NB, bool SHARED>
 hipError_t launch_few(FewArgs a, hipStream_t stream) {
   a.tiles_m = cdiv(a.g.K, TM);
   a.tiles_n = cdiv(a.g.N * a.g.P * a.g.Q, TN);
-  hipLaunchKernelGGL((conv_few_kernel<T, TM, TN, NW, NB>), dim3(a.tiles_m * a.tiles_n),
-                     dim3(NW * 64), 0, stream, a);
+  const dim3 grid(a.tiles_m * a.tiles_n);
+  if constexpr (SHARED)
+    hipLaunchKernelGGL((conv_few_shared_kernel<T, TM, TN, NW, NB>), grid,
+                       dim3(NW * (TM / 32) * (TN / 32) * 64), 0, stream, a);
+  else
+    hipLaunchKernelGGL((conv_few_kernel<T, TM, TN, NW, NB>), grid, dim3(NW * 64), 0, stream, a);
   return hipGetLastError();
 }
 
@@ -209,10 +342,10 @@ template <typename T> hipError_t dispatch_few(const FewArgs& a, hipStream_t stre
     }
   }
   switch (best) {
-    case 0: return launch_few<T, 64, 64, 4, 2>(a, stream);
-    case 1: return launch_few<T, 32, 64, 4, 3>(a, stream);
-    case 2: return launch_few<T, 32, 32, 8, 2>(a, stream);
-    default: return launch_few<T, 16, 32, 8, 3>(a, stream);
+    case 0: return launch_few<T, 64, 64, 2, 4, true>(a, stream);
+    case 1: return launch_few<T, 32, 64, 4, 3, true>(a, stream);
+    case 2: return launch_few<T, 32, 32, 8, 2, false>(a, stream);
+    default: return launch_few<T, 16, 32, 8, 3, false>(a, stream);
   }
 }
 
@@ -221,13 +354,16 @@ template <typename T> hipError_t dispatch_few(const FewArgs& a, hipStream_t stre
 bool conv_few_ok(int dt, const ConvGeom& g) {
   const int se = 8 * dtype_vec(dt);
   const long long npix = (long long)g.N * g.P * g.Q, red = (long long)g.R * g.S * g.C;
-  // At least one stage per wave; at most two 64 x 64 tiles per CU: at 512 tiles
-  // (256 channels x 8192 pixels) it is a third faster than split or
-  // half-filled large tiles, at 784 (12544 pixels) 42.6 against 31.4 us.  fp32,
-  // bound by the MFMAs there, gains up to 400 tiles (93 against 107 us) and
-  // loses at 512 (64 channels x 32768 pixels: 35.0 against 32.8).
-  return g.N > 0 && g.C % se == 0 && g.K % 4 == 0 && red >= 8 * se && red < (1 << 24) &&
-         cdiv(g.K, 64) * cdivl(npix, 64) <= (dt == DT_F32 ? 448 : 512);
+  // At most two 64 x 64 tiles per CU: at 512 tiles (256 channels x 8192 pixels)
+  // it is a third faster than split or half-filled large tiles, at 784 (12544
+  // pixels) 42.6 against 31.4 us.  fp32, bound by the MFMAs there, gains up to
+  // 400 tiles (93 against 107 us) and loses at 512 (64 channels x 32768 pixels:
+  // 35.0 against 32.8).  With fewer stages than waves (1 x 1 filters) half a
+  // tile per CU: 64 -> 128 channels at 3136 pixels (98 tiles) 5.1 -> 4.4 us, at
+  // 14400 (450) 4.3 -> 6.6.
+  const long long most = red < 8 * se ? 128 : dt == DT_F32 ? 448 : 512;
+  return g.N > 0 && g.C % se == 0 && g.K % 4 == 0 && red < (1 << 24) &&
+         cdiv(g.K, 64) * cdivl(npix, 64) <= most;
 }
 
 hipError_t conv_few_fwd(int dt, const ConvGeom& g, const void* x, const void* w, void* y,
