@@ -15,7 +15,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 BUILD = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libekya.so")
-SOURCES = ["conv.hip", "conv_few.hip", "elementwise.hip", "linear.hip", "weights.hip", "net.cpp", "rng.cpp", "runtime.cpp", "curve.cpp", "sched.cpp",
+SOURCES = ["conv.hip", "conv_few.hip", "elementwise.hip", "linear.hip", "stem_pool.hip", "weights.hip", "net.cpp", "rng.cpp", "runtime.cpp", "curve.cpp", "sched.cpp",
            "abi.cpp"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Wall", "-Wno-unused-result",

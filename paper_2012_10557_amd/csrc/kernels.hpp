@@ -102,21 +102,15 @@ hipError_t conv_few_fwd(int dt, const ConvGeom& g, const void* x, const void* w,
 hipError_t conv_fwd(int dt, const ConvGeom& g, const void* x, const void* w_krsc, void* y,
                     const ConvEpilogue& epi, float* ws, size_t ws_floats, hipStream_t stream,
                     BnStatsSink* sink = nullptr);
-// The 7x7/2 stem reading [.][H][W][3] frames directly (image n at idx[n] when
-// idx != null) in place of the padded input; g is the padded-input geometry
-// (C = 8).  bf16 with Q <= 112 only (stem_frames_ok).
-bool stem_frames_ok(int dt, const ConvGeom& g);
-// The stem (epilogue as given, e.g. folded BatchNorm + ReLU) followed by the
-// 3x3 / stride 2 / pad 1 max pool, in one kernel: y is [N][(P-1)/2+1][(Q-1)/2+1][64].
-// x is the padded input, or with `raw` the 3-channel frames as in
-// stem_fwd_frames.  bf16 with Q <= 112 only (stem_pool_ok).
+// The 7x7 / 2 stem with the epilogue (folded BatchNorm, ReLU; no residual) and
+// the 3x3 / stride 2 / pad 1 max pool in one kernel, reading [.][H][W][3] bf16
+// frames (image n at idx[n] when idx != null): y is
+// [N][(P-1)/2+1][(Q-1)/2+1][64], w the [64][7][7][8] copy.  g is the geometry
+// of the padded input (C = 8); bf16 with Q <= 112 only (stem_pool_ok).
 bool stem_pool_ok(int dt, const ConvGeom& g);
-hipError_t stem_pool_fwd(int dt, const ConvGeom& g, const void* x, bool raw, const int32_t* idx,
+hipError_t stem_pool_fwd(int dt, const ConvGeom& g, const void* frames, const int32_t* idx,
                          const void* w_krsc, void* y, const ConvEpilogue& epi,
                          hipStream_t stream);
-hipError_t stem_fwd_frames(int dt, const ConvGeom& g, const void* frames, const int32_t* idx,
-                           const void* w_krsc, void* y, const ConvEpilogue& epi,
-                           hipStream_t stream);
 // dx[N,H,W,C] = conv-transpose of dy[N,P,Q,K] with wT[C,R,S,K] (+ res[N,H,W,C]).
 // Needs K a multiple of 64 (bf16) / 32 (fp32) and stride 1 or 2.
 hipError_t conv_dgrad(int dt, const ConvGeom& g, const void* dy, const void* w_crsk, void* dx,

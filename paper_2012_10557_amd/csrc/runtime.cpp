@@ -405,12 +405,13 @@ static inline void* shadow_at(const Net& net, void* shadow, long long off) {
 // Run stages lo..hi in eval mode (BatchNorm folded into the conv epilogue) on
 // n frames.  Output: hi <= 3: the stage's output tensor; hi == 4: the pooled
 // fp32 features [n, 512]; hi == 5: fp32 logits [n, classes].
-// raw: x (stage 0 only) is [.][H][W][3] frames, image i at raw_idx[i] when
-// raw_idx != null, read directly by the stem (stem_frames_ok).
+// Stage 0's x is [.][H][W][3] frames, image i at frame_idx[i] when frame_idx !=
+// null, where the stem reads them itself (stem_pool_ok), else the padded
+// input.
 static hipError_t eval_forward(const Net& net, const Geo& g, const void* shadow, const float* fold,
                                const float* master, int lo, int hi, const void* x, int n,
-                               EvalBufs& b, void* out, hipStream_t st, bool raw = false,
-                               const int32_t* raw_idx = nullptr) {
+                               EvalBufs& b, void* out, hipStream_t st,
+                               const int32_t* frame_idx = nullptr) {
   const int dt = net.dt;
   const void* cur = x;
   auto fold_scale = [&](int bi) { return fold + 2 * net.bn[bi].st; };
@@ -424,17 +425,13 @@ static hipError_t eval_forward(const Net& net, const Geo& g, const void* shadow,
       void* dst = (hi == 0) ? out : b.p0;
       const ConvGeom cg = conv_geom(net, g, 0, n);
       if (stem_pool_ok(dt, cg)) {  // stem and max pool in one kernel
-        EKYA_HIP(stem_pool_fwd(dt, cg, cur, raw, raw_idx,
+        EKYA_HIP(stem_pool_fwd(dt, cg, cur, frame_idx,
                                shadow_at(net, shadow, net.conv[0].sh_krsc), dst, e, st));
         cur = dst;
         continue;
       }
-      if (raw)
-        EKYA_HIP(stem_fwd_frames(dt, cg, cur, raw_idx, shadow_at(net, shadow, net.conv[0].sh_krsc),
-                                 b.t1, e, st));
-      else
-        EKYA_HIP(conv_fwd(dt, cg, cur, shadow_at(net, shadow, net.conv[0].sh_krsc), b.t1, e, b.ws,
-                          b.ws_floats, st));
+      EKYA_HIP(conv_fwd(dt, cg, cur, shadow_at(net, shadow, net.conv[0].sh_krsc), b.t1, e, b.ws,
+                        b.ws_floats, st));
       EKYA_HIP(maxpool_fwd(dt, b.t1, n, g.sh, g.sw, 64, dst, nullptr, st));
       cur = dst;
     } else if (s <= 4) {
@@ -1162,9 +1159,9 @@ static hipError_t build_cache(const Net& net, const Geo& g, const void* shadow, 
     const int cnt = std::min(per, n - i0);
     const void* src = d_idx ? frames : reinterpret_cast<const char*>(frames) + i0 * fbytes;
     void* out = reinterpret_cast<char*>(cache) + (row0 + i0) * row_bytes;
-    if (stem_frames_ok(net.dt, conv_geom(net, g, 0, cnt))) {  // the stem reads the frames
+    if (stem_pool_ok(net.dt, conv_geom(net, g, 0, cnt))) {  // the stem reads the frames
       EKYA_HIP(eval_forward(net, g, shadow, fold, master, 0, lowest - 1, src, cnt, eb, out, st,
-                            true, d_idx ? d_idx + i0 : nullptr));
+                            d_idx ? d_idx + i0 : nullptr));
       continue;
     }
     EKYA_HIP(frames_to_padded(net.dt, src, d_idx ? d_idx + i0 : nullptr, cnt, g.H, g.W,
@@ -1256,10 +1253,12 @@ static hipError_t job_epochs(TrainJob& j) {
       const int cnt = std::min(j.eval_cap, j.n_h - h0);
       const void* in;
       if (j.lowest == 0) {
-        EKYA_HIP(frames_to_padded(j.dt, reinterpret_cast<const char*>(j.hframes) + h0 * fbytes,
-                                  nullptr, cnt, j.geo.H, j.geo.W, net.conv[0].cin_pad, j.eval_in,
-                                  qe));
-        in = j.eval_in;
+        in = reinterpret_cast<const char*>(j.hframes) + h0 * fbytes;
+        if (!stem_pool_ok(j.dt, conv_geom(net, j.geo, 0, cnt))) {
+          EKYA_HIP(frames_to_padded(j.dt, in, nullptr, cnt, j.geo.H, j.geo.W, net.conv[0].cin_pad,
+                                    j.eval_in, qe));
+          in = j.eval_in;
+        }
       } else {
         in = reinterpret_cast<const char*>(j.hcache) + (long long)h0 * j.row_bytes;
       }
@@ -1797,16 +1796,16 @@ static hipError_t infer_frames(const Net& net, const Geo& geo, const float* mast
   for (int i0 = 0; i0 < n; i0 += per) {
     const int cnt = std::min(per, n - i0);
     const void* src = reinterpret_cast<const char*>(frames) + i0 * fbytes;
-    const bool raw_ok = stem_frames_ok(net.dt, conv_geom(net, geo, 0, cnt));
+    const bool raw_ok = stem_pool_ok(net.dt, conv_geom(net, geo, 0, cnt));
     if (resolution == H && resolution == W && raw_ok) {
-      EKYA_HIP(eval_forward(net, geo, shadow, fold, master, 0, 5, src, cnt, eb, eb.logits, stream,
-                            true));  // the stem reads the frames
+      EKYA_HIP(eval_forward(net, geo, shadow, fold, master, 0, 5, src, cnt, eb, eb.logits,
+                            stream));  // the stem reads the frames
     } else if (raw_ok) {
       // resized to 3-channel frames, which the stem reads as it reads the
       // originals (the same staged bytes as an 8-channel padded copy)
       EKYA_HIP(resize_to_padded(net.dt, src, cnt, H, W, resolution, 3, ib.padded, stream));
       EKYA_HIP(eval_forward(net, geo, shadow, fold, master, 0, 5, ib.padded, cnt, eb, eb.logits,
-                            stream, true));
+                            stream));
     } else {
       if (resolution == H && resolution == W)
         EKYA_HIP(frames_to_padded(net.dt, src, nullptr, cnt, H, W, net.conv[0].cin_pad, ib.padded,
