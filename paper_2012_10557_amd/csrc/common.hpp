@@ -86,6 +86,32 @@ __device__ __forceinline__ void mma_unit(f32x4& acc, uint4 a, uint4 b, float*) {
   acc = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(a.w), __uint_as_float(b.w), acc, 0, 0, 0);
 }
 
+// acc[i][j] += A_i B_j over one unit of each operand.  For fp32 the four MFMA
+// steps of a unit are the outer loop, so that consecutive MFMAs are
+// independent; each tile's steps keep their order.
+template <int TI, int TJ>
+__device__ __forceinline__ void mma_tile(f32x4 (&acc)[TI][TJ], const uint4 (&a)[TI],
+                                         const uint4 (&b)[TJ], bf16* t) {
+#pragma unroll
+  for (int i = 0; i < TI; ++i)
+#pragma unroll
+    for (int j = 0; j < TJ; ++j) mma_unit(acc[i][j], a[i], b[j], t);
+}
+template <int TI, int TJ>
+__device__ __forceinline__ void mma_tile(f32x4 (&acc)[TI][TJ], const uint4 (&a)[TI],
+                                         const uint4 (&b)[TJ], float*) {
+#pragma unroll
+  for (int e = 0; e < 4; ++e)
+#pragma unroll
+    for (int i = 0; i < TI; ++i)
+#pragma unroll
+      for (int j = 0; j < TJ; ++j) {
+        const float x = __uint_as_float(e == 0 ? a[i].x : e == 1 ? a[i].y : e == 2 ? a[i].z : a[i].w);
+        const float y = __uint_as_float(e == 0 ? b[j].x : e == 1 ? b[j].y : e == 2 ? b[j].z : b[j].w);
+        acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(x, y, acc[i][j], 0, 0, 0);
+      }
+}
+
 // Transpose an E x E block held as E units (unit i = row i) into E units
 // (unit j = column j).
 __device__ __forceinline__ void transpose_block(uint4 (&v)[4], float*) {

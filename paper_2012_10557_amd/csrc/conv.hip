@@ -53,6 +53,7 @@ struct BnEpi {
 };
 
 // Stores v as bf16 and leaves the stored (rounded) values in v.
+__device__ __forceinline__ void store4_keep(float* dst, float (&v)[4]) { store4<float>(dst, v); }
 __device__ __forceinline__ void store4_keep(bf16* dst, float (&v)[4]) {
   store4<bf16>(dst, v);
 #pragma unroll
@@ -604,33 +605,37 @@ __host__ __device__ __forceinline__ int xcd_tile(int L, int total) {
   return x * (total >> 3) + min(x, total & 7) + k;
 }
 
-struct DmaFwdArgs {
+template <typename T> struct DmaFwdArgsT {
   ConvGeom g;
-  const bf16* x;
-  const bf16* w;  // [K][R][S][C]
-  bf16* y;
+  const T* x;
+  const T* w;  // [K][R][S][C]
+  T* y;
   ConvEpilogue epi;
   SplitOut so;
   int tiles_m, tiles_n;
   BnEpi bn;
 };
 
-template <int BM, int BN>
-struct DmaFwdOp {
+// A stage is 8 units (128 bytes) of every row: SE = 64 bf16 or 32 fp32
+// reduction elements.
+template <typename T, int BM, int BN>
+struct DmaFwdOpT {
+  static constexpr int E = Elt<T>::E, SE = 8 * E;
+  using Elem = T;
   static constexpr int GA = BM / 8, IPW = (BM + BN) / 32;  // row octets per wave
-  using Args = DmaFwdArgs;
+  using Args = DmaFwdArgsT<T>;
   int s_begin, s_end;
   long long Ktot;
-  const bf16* ptr[IPW];
+  const T* ptr[IPW];
   int h0[IPW], w0[IPW];
   int rowoff[IPW];  // input pixel (h0, w0) within its image, in elements (may be negative)
   bool ok[IPW];
   int tr, ts, tc;
   int split;
 
-  // reduction stages [s0, s1) of a split: 64-element steps of R*S*C
+  // reduction stages [s0, s1) of a split: SE-element steps of R*S*C
   static __device__ void stage_range(const Args& a, int split, int n0, int& s0, int& s1) {
-    const int ns = a.g.R * a.g.S * a.g.C / 64;
+    const int ns = a.g.R * a.g.S * a.g.C / SE;
     s0 = min(ns, split * a.so.stages_per_split);
     s1 = min(ns, s0 + a.so.stages_per_split);
   }
@@ -648,7 +653,7 @@ struct DmaFwdOp {
       if (oct < GA) {
         const int row = m0 + oct * 8 + r8;
         ok[j] = row < g.K;
-        ptr[j] = a.w + (ok[j] ? row : 0) * Ktot + u * 8;
+        ptr[j] = a.w + (ok[j] ? row : 0) * Ktot + u * E;
         h0[j] = w0[j] = rowoff[j] = 0;
       } else {
         const int pix = n0 + (oct - GA) * 8 + r8;
@@ -659,10 +664,10 @@ struct DmaFwdOp {
         h0[j] = p * g.stride - g.pad;
         w0[j] = q * g.stride - g.pad;
         rowoff[j] = (h0[j] * g.W + w0[j]) * g.C;
-        ptr[j] = a.x + (long long)n * g.H * g.W * g.C + u * 8;
+        ptr[j] = a.x + (long long)n * g.H * g.W * g.C + u * E;
       }
     }
-    const int k0 = s_begin * 64;
+    const int k0 = s_begin * SE;
     const int rs = k0 / g.C;
     tc = k0 - rs * g.C;
     tr = rs / g.S;
@@ -672,7 +677,7 @@ struct DmaFwdOp {
   // 32-bit offset; the tap's part (tr W + ts) C + tc is wave-uniform.
   __device__ void issue(const Args& a, int st, uint4* slot, int wave, const void* zero) {
     const ConvGeom& g = a.g;
-    const long long k0 = (long long)st * 64;
+    const long long k0 = (long long)st * SE;
     const int tap = (tr * g.W + ts) * g.C + tc;
 #pragma unroll
     for (int j = 0; j < IPW; ++j) {
@@ -687,7 +692,7 @@ struct DmaFwdOp {
       }
       dma16(src, slot + oct * 64);
     }
-    tc += 64;
+    tc += SE;
     if (tc >= g.C) {
       tc = 0;
       if (++ts == g.S) {
@@ -720,7 +725,7 @@ struct DmaFwdOp {
     }
     if (e.res) {
       float r[4];
-      load4<bf16>(reinterpret_cast<const bf16*>(e.res) + off, r);
+      load4<T>(reinterpret_cast<const T*>(e.res) + off, r);
 #pragma unroll
       for (int i = 0; i < 4; ++i) v[i] += r[i];
     }
@@ -732,35 +737,39 @@ struct DmaFwdOp {
     return true;
   }
 };
+template <int BM, int BN> using DmaFwdOp = DmaFwdOpT<bf16, BM, BN>;
+template <int BM, int BN> using DmaFwdOpF = DmaFwdOpT<float, BM, BN>;
 
-struct DmaDgradArgs {
+template <typename T> struct DmaDgradArgsT {
   ConvGeom g;
-  const bf16* dy;
-  const bf16* wt;  // [C][R][S][K]
-  bf16* dx;
-  const bf16* res;
+  const T* dy;
+  const T* wt;  // [C][R][S][K]
+  T* dx;
+  const T* res;
   SplitOut so;
   int tiles_m, tiles_n;
   BnEpi bn;
 };
 
 // dx[pix][c] = sum_(r,s,k) wt[c][r][s][k] dy(pix; r,s,k), stride 1 or 2.
-template <int BM, int BN>
-struct DmaDgradOp {
+template <typename T, int BM, int BN>
+struct DmaDgradOpT {
+  static constexpr int E = Elt<T>::E, SE = 8 * E;
+  using Elem = T;
   static constexpr int GA = BM / 8, IPW = (BM + BN) / 32;
-  using Args = DmaDgradArgs;
+  using Args = DmaDgradArgsT<T>;
   int s_begin, s_end;
   long long Ktot;
-  const bf16* ptr[IPW];
+  const T* ptr[IPW];
   int hp[IPW], wp[IPW];  // input pixel + pad
   int rowoff[IPW];       // stride 1: output-gradient pixel (hp, wp), in elements
   bool ok[IPW];
   int tr, ts, tk;
   int split;
 
-  // reduction stages [s0, s1) of a split: 64-element steps of R*S*K
+  // reduction stages [s0, s1) of a split: SE-element steps of R*S*K
   static __device__ void stage_range(const Args& a, int split, int n0, int& s0, int& s1) {
-    const int ns = a.g.R * a.g.S * a.g.K / 64;
+    const int ns = a.g.R * a.g.S * a.g.K / SE;
     s0 = min(ns, split * a.so.stages_per_split);
     s1 = min(ns, s0 + a.so.stages_per_split);
   }
@@ -778,7 +787,7 @@ struct DmaDgradOp {
       if (oct < GA) {
         const int row = m0 + oct * 8 + r8;
         ok[j] = row < g.C;
-        ptr[j] = a.wt + (ok[j] ? row : 0) * Ktot + u * 8;
+        ptr[j] = a.wt + (ok[j] ? row : 0) * Ktot + u * E;
         hp[j] = wp[j] = rowoff[j] = 0;
       } else {
         const int pix = n0 + (oct - GA) * 8 + r8;
@@ -788,10 +797,10 @@ struct DmaDgradOp {
         hp[j] = rem / g.W + g.pad;
         wp[j] = rem % g.W + g.pad;
         rowoff[j] = (hp[j] * g.Q + wp[j]) * g.K;
-        ptr[j] = a.dy + (long long)n * g.P * g.Q * g.K + u * 8;
+        ptr[j] = a.dy + (long long)n * g.P * g.Q * g.K + u * E;
       }
     }
-    const int k0 = s_begin * 64;
+    const int k0 = s_begin * SE;
     const int rs = k0 / g.K;
     tk = k0 - rs * g.K;
     tr = rs / g.S;
@@ -801,7 +810,7 @@ struct DmaDgradOp {
   // plus a wave-uniform one; stride 2: (h / 2, w / 2) for even h and w.
   __device__ void issue(const Args& a, int st, uint4* slot, int wave, const void* zero) {
     const ConvGeom& g = a.g;
-    const long long k0 = (long long)st * 64;
+    const long long k0 = (long long)st * SE;
     const int tap = tk - (tr * g.Q + ts) * g.K;
 #pragma unroll
     for (int j = 0; j < IPW; ++j) {
@@ -822,7 +831,7 @@ struct DmaDgradOp {
       }
       dma16(src, slot + oct * 64);
     }
-    tk += 64;
+    tk += SE;
     if (tk >= g.K) {
       tk = 0;
       if (++ts == g.S) {
@@ -845,7 +854,7 @@ struct DmaDgradOp {
     }
     if (a.res) {
       float r[4];
-      load4<bf16>(a.res + off, r);
+      load4<T>(a.res + off, r);
 #pragma unroll
       for (int i = 0; i < 4; ++i) v[i] += r[i];
     }
@@ -853,6 +862,8 @@ struct DmaDgradOp {
     return true;
   }
 };
+template <int BM, int BN> using DmaDgradOp = DmaDgradOpT<bf16, BM, BN>;
+template <int BM, int BN> using DmaDgradOpF = DmaDgradOpT<float, BM, BN>;
 
 // Stride-2 data gradient by parity class.  Input pixel (h, w) = (2 i + ph,
 // 2 j + pw) receives exactly the taps r = r0, r0 + 2, ... (r0 = (ph + pad)
@@ -900,6 +911,7 @@ __host__ __device__ inline S2Class s2_class(const ConvGeom& g, int cls) {
 
 template <int BM, int BN>
 struct DmaDgradS2Op {
+  using Elem = bf16;
   static constexpr int GA = BM / 8, IPW = (BM + BN) / 32;
   using Args = DmaDgradS2Args;
   int s_begin, s_end;
@@ -1260,10 +1272,7 @@ __global__ __launch_bounds__(NT) void gemm_dma_kernel(typename Op::Args a) {
       for (int i = 0; i < TI; ++i) fa[i] = As[i * 128 + off];
 #pragma unroll
       for (int j = 0; j < TJ; ++j) fb[j] = Bs[j * 128 + off];
-#pragma unroll
-      for (int i = 0; i < TI; ++i)
-#pragma unroll
-        for (int j = 0; j < TJ; ++j) mma_unit(acc[i][j], fa[i], fb[j], (bf16*)nullptr);
+      mma_tile(acc, fa, fb, (typename Op::Elem*)nullptr);
     }
     if (++slot == NST) slot = 0;
   }
@@ -1353,10 +1362,7 @@ __global__ __launch_bounds__((BM / WTM) * (BN / WTN) * 64 + WS_LOADERS * 64) voi
       for (int i = 0; i < TI; ++i) fa[i] = As[i * 128 + off];
 #pragma unroll
       for (int j = 0; j < TJ; ++j) fb[j] = Bs[j * 128 + off];
-#pragma unroll
-      for (int i = 0; i < TI; ++i)
-#pragma unroll
-        for (int j = 0; j < TJ; ++j) mma_unit(acc[i][j], fa[i], fb[j], (bf16*)nullptr);
+      mma_tile(acc, fa, fb, (typename Op::Elem*)nullptr);
     }
     stage_barrier();
     if (++slot == NST) slot = 0;
@@ -2812,8 +2818,8 @@ hipError_t launch_dma(typename OpT<BM, BN>::Args a, long long cols, int rows, hi
   hipError_t e = hipGetLastError();
   if (t && e == hipSuccess) {
     EKYA_HIP(hipEventRecord(e1, stream));
-    t->recs.push_back({std::string(name) + "<bf16," + std::to_string(BM) + "," +
-                           std::to_string(BN) + ",dma>",
+    t->recs.push_back({std::string(name) + "<" + tname<typename OpT<BM, BN>::Elem>() + "," +
+                           std::to_string(BM) + "," + std::to_string(BN) + ",dma>",
                        cost.flops, cost.bytes, e0, e1});
   }
   return e;
@@ -2870,6 +2876,26 @@ hipError_t dispatch_dma(Args a, const DmaPlan& p, long long cols, int rows, hipS
   if (p.bm == 64 && p.bn == 256) return launch_dma<64, 256, 1, OpT>(a, cols, rows, stream, cost, name);
   if (p.bm == 64 && p.bn == 128) return launch_dma<64, 128, 1, OpT>(a, cols, rows, stream, cost, name);
   return hipErrorInvalidValue;
+}
+
+// fp32 forward and data gradient: 64 x 64 direct-to-LDS tiles.  fp32 is bound
+// by its MFMAs (a sixteenth of the bf16 rate: a stage's 16 KB are a thousand
+// clocks of MFMAs per wave), so a small tile loses nothing and spreads evenly,
+// five blocks (20 waves) per CU overlapping each other's waits.  Against the
+// register-staged tiles of plan_tiles (3 x 3, fp32): 96 images at 224, layer
+// 1 260 -> 229 us, layer 2 269 -> 235, layer 3 287 -> 235, layer 4 277 -> 255
+// (115 TFLOP/s at layer 2; a large matrix product reaches 155); 150 images at
+// 160, 201 -> 174, 190 -> 180, 194 -> 180, 200 -> 180.  128 x 64 is 5% faster
+// where its tiles fill the last wave (layer 2 at 224) and up to 25% slower
+// where they do not (layer 4, 296 tiles on 256 CUs); 128 x 128 more so on
+// both sides.  The data gradient with its filter packing: 96 images, 28 x 28 x
+// 128 306 -> 238 us, 14 x 14 x 256 385 -> 276, stride 2 to 28 x 28 x 128 584
+// -> 462.  Below 449 tiles conv_few_fwd takes the forward pass, and the data
+// gradient keeps plan_tiles' split reductions, which fill the chip.
+// Offsets within an image are 32-bit.
+bool f32_dma_ok(int rows, long long cols, int red_channels, long long image_elems) {
+  return red_channels % 32 == 0 && image_elems < (1LL << 31) &&
+         cdiv(rows, 64) * cdivl(cols, 64) > 448;
 }
 
 // Whether the kernel dispatch_dma runs for an unsplit plan has a variant that
@@ -2944,7 +2970,8 @@ hipError_t conv_fwd_dma(const ConvGeom& g, const void* x, const void* w, void* y
       cdiv(g.K, 128) * cdivl(npix, 128) < 512)
     p.bn = 64;
   if (p.splits > 1 && (size_t)p.splits * npix * g.K > ws_floats) p = {p.bm, p.bn, 1, ns, p.ws};
-  DmaFwdArgs a{g, (const bf16*)x, (const bf16*)w, (bf16*)y, epi, SplitOut{ws, p.splits, p.sps}, 0, 0};
+  DmaFwdArgsT<bf16> a{g, (const bf16*)x, (const bf16*)w, (bf16*)y, epi,
+                      SplitOut{ws, p.splits, p.sps}, 0, 0};
   const bool plain = !epi.scale && !epi.shift && !epi.res && !epi.relu;
   const bool bn_epi = sink && !sink->bwd && sink->part && plain && plan_bn_epilogue(p) &&
                       bn_fold_path(npix, g.K);
@@ -3032,8 +3059,8 @@ hipError_t conv_dgrad_dma(const ConvGeom& g, const void* dy, const void* wt, voi
     return conv_dgrad_s2(g, dy, wt, dx, res, ws, ws_floats, stream);
   DmaPlan p = plan_dma(g.C, npix, ns, ws != nullptr);
   if (p.splits > 1 && (size_t)p.splits * npix * g.C > ws_floats) p = {p.bm, p.bn, 1, ns, p.ws};
-  DmaDgradArgs a{g, (const bf16*)dy, (const bf16*)wt, (bf16*)dx, (const bf16*)res,
-                 SplitOut{ws, p.splits, p.sps}, 0, 0};
+  DmaDgradArgsT<bf16> a{g, (const bf16*)dy, (const bf16*)wt, (bf16*)dx, (const bf16*)res,
+                           SplitOut{ws, p.splits, p.sps}, 0, 0};
   const bool bn_epi = sink && sink->bwd && sink->part && sink->z && sink->mean &&
                       plan_bn_epilogue(p) && bn_fold_path(npix, g.C);
   if (bn_epi) {
@@ -3090,6 +3117,14 @@ hipError_t conv_fwd_t(const ConvGeom& g, const void* x, const void* w, void* y,
   }
   if (sizeof(T) == 4 && conv_few_ok(DT_F32, g))
     return conv_few_fwd(DT_F32, g, x, w, y, epi, stream);
+  if (sizeof(T) == 4 &&
+      f32_dma_ok(g.K, (long long)g.N * g.P * g.Q, g.C, (long long)g.H * g.W * g.C)) {
+    DmaFwdArgsT<float> a{g, (const float*)x, (const float*)w, (float*)y, epi,
+                         SplitOut{nullptr, 1, g.R * g.S * g.C / 32}, 0, 0};
+    return launch_dma<64, 64, 2, DmaFwdOpF>(a, (long long)g.N * g.P * g.Q, g.K, stream,
+                                           conv_cost(g, g.C0 ? g.C0 : g.C, sizeof(T), false),
+                                           "conv_fwd");
+  }
   const bool ut = g.C % (KU_MAIN * E) == 0;
   const int ns = cdiv(g.R * g.S * g.C, KU_MAIN * E);
   const long long npix = (long long)g.N * g.P * g.Q;
@@ -3125,6 +3160,12 @@ hipError_t conv_dgrad_t(const ConvGeom& g, const void* dy, const void* wt, void*
   if (sizeof(T) == 2) return conv_dgrad_dma(g, dy, wt, dx, res, ws, ws_floats, stream, sink);
   const int ns = cdiv(g.R * g.S * g.K, KU_MAIN * E);
   const long long npix = (long long)g.N * g.H * g.W;
+  if (sizeof(T) == 4 && f32_dma_ok(g.C, npix, g.K, (long long)g.P * g.Q * g.K)) {
+    DmaDgradArgsT<float> a{g, (const float*)dy, (const float*)wt, (float*)dx, (const float*)res,
+                           SplitOut{nullptr, 1, ns}, 0, 0};
+    return launch_dma<64, 64, 2, DmaDgradOpF>(a, npix, g.C, stream,
+                                             conv_cost(g, g.C, sizeof(T), false), "conv_dgrad");
+  }
   Plan p = plan_tiles(g.C, (int)npix, ns, ws != nullptr);
   if (p.splits > 1 && (size_t)p.splits * npix * g.C > ws_floats) {
     p.splits = 1;

@@ -185,11 +185,7 @@ __global__ __launch_bounds__(NW * 64) void conv_few_kernel(FewArgs a) {
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
     if (st + NB < s1) issue(st + NB, slot);
 #pragma unroll
-    for (int kf = 0; kf < 2; ++kf)
-#pragma unroll
-      for (int i = 0; i < TI; ++i)
-#pragma unroll
-        for (int j = 0; j < TJ; ++j) mma_unit(acc[i][j], fa[kf][i], fb[kf][j], (T*)nullptr);
+    for (int kf = 0; kf < 2; ++kf) mma_tile(acc, fa[kf], fb[kf], (T*)nullptr);
     slot += SU;
     if (slot == ring + NB * SU) slot = ring;
   }
@@ -294,10 +290,7 @@ __global__ __launch_bounds__(NG * (TM / 32) * (TN / 32) * 64) void conv_few_shar
         for (int i = 0; i < 2; ++i) fa[i] = As[i * 128 + off[kf]];
 #pragma unroll
         for (int j = 0; j < 2; ++j) fb[j] = Bs[j * 128 + off[kf]];
-#pragma unroll
-        for (int i = 0; i < 2; ++i)
-#pragma unroll
-          for (int j = 0; j < 2; ++j) mma_unit(acc[i][j], fa[i], fb[j], (T*)nullptr);
+        mma_tile(acc, fa, fb, (T*)nullptr);
       }
     }
     if (++slot == NB) slot = 0;
