@@ -355,7 +355,9 @@ bool conv_few_ok(int dt, const ConvGeom& g) {
   // tile per CU: 64 -> 128 channels at 3136 pixels (98 tiles) 5.1 -> 4.4 us, at
   // 14400 (450) 4.3 -> 6.6.
   const long long most = red < 8 * se ? 128 : dt == DT_F32 ? 448 : 512;
+  // Offsets within an image are 32-bit.
   return g.N > 0 && g.C % se == 0 && g.K % 4 == 0 && red < (1 << 24) &&
+         ((long long)g.H + 2 * g.pad) * g.W * g.C < (1LL << 31) &&
          cdiv(g.K, 64) * cdivl(npix, 64) <= most;
 }
 

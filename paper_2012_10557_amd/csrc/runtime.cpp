@@ -62,8 +62,16 @@ hipError_t EventPool::take(bool timing, hipEvent_t* e) {
 
 void EventPool::give(bool timing, hipEvent_t& e) {
   if (!e) return;
-  std::lock_guard<std::mutex> lk(mu);
-  (timing ? timed : plain).push_back(e);
+  {
+    std::lock_guard<std::mutex> lk(mu);
+    std::vector<hipEvent_t>& v = timing ? timed : plain;
+    if (v.size() < kMost) {
+      v.push_back(e);
+      e = nullptr;
+      return;
+    }
+  }
+  (void)hipEventDestroy(e);
   e = nullptr;
 }
 

@@ -41,8 +41,10 @@ struct PlanMemo {
 
 // Events kept between a context's calls (creating and destroying a
 // retraining job's took about 0.2 ms per call).  Candidates of one profiling
-// call take theirs from several threads.
+// call take theirs from several threads.  At most kMost of a kind are kept:
+// a sweep of 16 candidates of a few epochs each uses fewer.
 struct EventPool {
+  static constexpr size_t kMost = 1024;
   std::mutex mu;
   std::vector<hipEvent_t> timed, plain;
   hipError_t take(bool timing, hipEvent_t* e);

@@ -34,3 +34,23 @@ def test_few_pixel_convolution_matches_float64(N, H, W, C, K, R, stride, prec):
     if prec == "bf16":
         bound = bound + 2.0 ** -8 * (ref.abs() + bound)
     assert ((y - ref).abs() <= bound + 1e-30).all()
+
+
+def test_image_beyond_32_bit_offsets():
+    """One float32 image of 2^31 elements, whose offsets need 64 bits."""
+    import torch
+    from paper_2012_10557_amd import binding
+    H, C, K, stride = 2048, 512, 4, 64
+    gen = torch.Generator(device="cuda").manual_seed(5)
+    x = torch.randn(1, H, H, C, generator=gen, device="cuda")
+    w = torch.randn(K, C, 3, 3, generator=gen, device="cuda")
+    y = binding.ekya_op_conv2d(x, w, stride, 1).double()
+    at = torch.arange(0, H, stride, device="cuda")
+    ref, mag = torch.zeros_like(y[0]), torch.zeros_like(y[0])
+    for r in range(3):
+        for s in range(3):
+            h, v = (at - 1 + r)[:, None], (at - 1 + s)[None, :]
+            px = x[0, h.clamp(min=0), v.clamp(min=0)].double() * ((h >= 0) & (v >= 0))[..., None]
+            ref += px @ w[:, :, r, s].double().T
+            mag += px.abs() @ w[:, :, r, s].double().abs().T
+    assert ((y[0] - ref).abs() <= C * 9 * 2.0 ** -24 * mag).all()
