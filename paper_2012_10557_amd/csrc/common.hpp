@@ -112,6 +112,53 @@ __device__ __forceinline__ void mma_tile(f32x4 (&acc)[TI][TJ], const uint4 (&a)[
       }
 }
 
+// acc += products, stage by stage (a stage: 8 units of each operand row, two
+// add calls).  A long chain of fp32 products in one accumulator rounds worse
+// than the shorter chains of a split reduction, so with RUN fp32 products go
+// to accumulators of their own, added to acc every RUN stages (32 products
+// each; 0: one chain).  Relative error against float64 (split reduction, one
+// chain, RUN 8, 4, 2): 256 channels at 14 x 14, 16 frames 2.5e-7, 4.2e-7,
+// 2.0e-7, 1.6e-7, 1.3e-7; 128 at 8 x 8, 48 frames 1.55e-7, 2.1e-7, 1.9e-7,
+// 1.47e-7, 1.2e-7: FP32_RUN is the longest that is nowhere further off than
+// the split reduction.
+constexpr int FP32_RUN = 4;
+template <typename T, int TI, int TJ, int RUN> struct RunSum {
+  static constexpr bool runs = sizeof(T) == 4 && RUN > 0;
+  f32x4 (&acc)[TI][TJ];
+  f32x4 part[TI][TJ];
+  int n = 0;
+  __device__ __forceinline__ RunSum(f32x4 (&a)[TI][TJ]) : acc(a) { clear(); }
+  __device__ __forceinline__ void clear() {
+    if constexpr (runs) {
+#pragma unroll
+      for (int i = 0; i < TI; ++i)
+#pragma unroll
+        for (int j = 0; j < TJ; ++j) part[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+    }
+  }
+  __device__ __forceinline__ void add(const uint4 (&a)[TI], const uint4 (&b)[TJ]) {
+    if constexpr (runs)
+      mma_tile(part, a, b, (T*)nullptr);
+    else
+      mma_tile(acc, a, b, (T*)nullptr);
+  }
+  __device__ __forceinline__ void flush() {
+    if constexpr (runs) {
+#pragma unroll
+      for (int i = 0; i < TI; ++i)
+#pragma unroll
+        for (int j = 0; j < TJ; ++j) acc[i][j] += part[i][j];
+    }
+  }
+  __device__ __forceinline__ void end_stage() {
+    if (runs && ++n == RUN) {
+      flush();
+      clear();
+      n = 0;
+    }
+  }
+};
+
 // Transpose an E x E block held as E units (unit i = row i) into E units
 // (unit j = column j).
 __device__ __forceinline__ void transpose_block(uint4 (&v)[4], float*) {

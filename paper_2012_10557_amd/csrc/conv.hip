@@ -618,9 +618,9 @@ template <typename T> struct DmaFwdArgsT {
 
 // A stage is 8 units (128 bytes) of every row: SE = 64 bf16 or 32 fp32
 // reduction elements.
-template <typename T, int BM, int BN>
+template <typename T, int BM, int BN, int RUN_ = 0>
 struct DmaFwdOpT {
-  static constexpr int E = Elt<T>::E, SE = 8 * E;
+  static constexpr int E = Elt<T>::E, SE = 8 * E, RUN = RUN_;  // RUN: see RunSum
   using Elem = T;
   static constexpr int GA = BM / 8, IPW = (BM + BN) / 32;  // row octets per wave
   using Args = DmaFwdArgsT<T>;
@@ -739,6 +739,7 @@ struct DmaFwdOpT {
 };
 template <int BM, int BN> using DmaFwdOp = DmaFwdOpT<bf16, BM, BN>;
 template <int BM, int BN> using DmaFwdOpF = DmaFwdOpT<float, BM, BN>;
+template <int BM, int BN> using DmaFwdOpRuns = DmaFwdOpT<float, BM, BN, FP32_RUN>;
 
 template <typename T> struct DmaDgradArgsT {
   ConvGeom g;
@@ -752,9 +753,9 @@ template <typename T> struct DmaDgradArgsT {
 };
 
 // dx[pix][c] = sum_(r,s,k) wt[c][r][s][k] dy(pix; r,s,k), stride 1 or 2.
-template <typename T, int BM, int BN>
+template <typename T, int BM, int BN, int RUN_ = 0>
 struct DmaDgradOpT {
-  static constexpr int E = Elt<T>::E, SE = 8 * E;
+  static constexpr int E = Elt<T>::E, SE = 8 * E, RUN = RUN_;  // RUN: see RunSum
   using Elem = T;
   static constexpr int GA = BM / 8, IPW = (BM + BN) / 32;
   using Args = DmaDgradArgsT<T>;
@@ -864,6 +865,7 @@ struct DmaDgradOpT {
 };
 template <int BM, int BN> using DmaDgradOp = DmaDgradOpT<bf16, BM, BN>;
 template <int BM, int BN> using DmaDgradOpF = DmaDgradOpT<float, BM, BN>;
+template <int BM, int BN> using DmaDgradOpRuns = DmaDgradOpT<float, BM, BN, FP32_RUN>;
 
 // Stride-2 data gradient by parity class.  Input pixel (h, w) = (2 i + ph,
 // 2 j + pw) receives exactly the taps r = r0, r0 + 2, ... (r0 = (ph + pad)
@@ -912,6 +914,7 @@ __host__ __device__ inline S2Class s2_class(const ConvGeom& g, int cls) {
 template <int BM, int BN>
 struct DmaDgradS2Op {
   using Elem = bf16;
+  static constexpr int RUN = 0;
   static constexpr int GA = BM / 8, IPW = (BM + BN) / 32;
   using Args = DmaDgradS2Args;
   int s_begin, s_end;
@@ -1252,6 +1255,7 @@ __global__ __launch_bounds__(NT) void gemm_dma_kernel(typename Op::Args a) {
     if (s0 + p < s1) op.issue(a, s0 + p, smem + p * SU, wave, zero);
 
   int slot = 0;
+  RunSum<typename Op::Elem, TI, TJ, Op::RUN> sum(acc);
   for (int st = s0; st < s1; ++st) {
     if (st + NST - 2 < s1)
       wait_vmcnt<LPS * (NST - 2)>();
@@ -1272,11 +1276,13 @@ __global__ __launch_bounds__(NT) void gemm_dma_kernel(typename Op::Args a) {
       for (int i = 0; i < TI; ++i) fa[i] = As[i * 128 + off];
 #pragma unroll
       for (int j = 0; j < TJ; ++j) fb[j] = Bs[j * 128 + off];
-      mma_tile(acc, fa, fb, (typename Op::Elem*)nullptr);
+      sum.add(fa, fb);
     }
+    sum.end_stage();
     if (++slot == NST) slot = 0;
   }
 
+  sum.flush();
   wave_epilogue<TI, TJ, BNS>(a, op, acc, m0 + wm * WM, n0 + wn * WN, lane);
 }
 
@@ -2897,6 +2903,14 @@ bool f32_dma_ok(int rows, long long cols, int red_channels, long long image_elem
   return red_channels % 32 == 0 && image_elems < (1LL << 31) &&
          cdiv(rows, 64) * cdivl(cols, 64) > 448;
 }
+// Below kTargetBlocks tiles, where the register-staged tiles would split the
+// reduction, its sums are kept in runs (RunSum): one chain of 2304 products
+// rounds to 5.9e-7 against float64, its split in three to 3.5e-7, runs to
+// 1.7e-7.  Runs in every tile would cost 96 images at 224 px 2.8% (3.92 ->
+// 4.04 ms per call); of 10 they take 1.4% (571 -> 579 us).
+bool f32_dma_runs(int rows, long long cols) {
+  return cdiv(rows, 64) * cdivl(cols, 64) < kTargetBlocks;
+}
 
 // Whether the kernel dispatch_dma runs for an unsplit plan has a variant that
 // leaves BatchNorm chunk statistics (launch_ws / launch_dma).
@@ -3121,9 +3135,11 @@ hipError_t conv_fwd_t(const ConvGeom& g, const void* x, const void* w, void* y,
       f32_dma_ok(g.K, (long long)g.N * g.P * g.Q, g.C, (long long)g.H * g.W * g.C)) {
     DmaFwdArgsT<float> a{g, (const float*)x, (const float*)w, (float*)y, epi,
                          SplitOut{nullptr, 1, g.R * g.S * g.C / 32}, 0, 0};
-    return launch_dma<64, 64, 2, DmaFwdOpF>(a, (long long)g.N * g.P * g.Q, g.K, stream,
-                                           conv_cost(g, g.C0 ? g.C0 : g.C, sizeof(T), false),
-                                           "conv_fwd");
+    const long long cols = (long long)g.N * g.P * g.Q;
+    const Cost cost = conv_cost(g, g.C0 ? g.C0 : g.C, sizeof(T), false);
+    return f32_dma_runs(g.K, cols)
+               ? launch_dma<64, 64, 2, DmaFwdOpRuns>(a, cols, g.K, stream, cost, "conv_fwd")
+               : launch_dma<64, 64, 2, DmaFwdOpF>(a, cols, g.K, stream, cost, "conv_fwd");
   }
   const bool ut = g.C % (KU_MAIN * E) == 0;
   const int ns = cdiv(g.R * g.S * g.C, KU_MAIN * E);
@@ -3163,8 +3179,10 @@ hipError_t conv_dgrad_t(const ConvGeom& g, const void* dy, const void* wt, void*
   if (sizeof(T) == 4 && f32_dma_ok(g.C, npix, g.K, (long long)g.P * g.Q * g.K)) {
     DmaDgradArgsT<float> a{g, (const float*)dy, (const float*)wt, (float*)dx, (const float*)res,
                            SplitOut{nullptr, 1, ns}, 0, 0};
-    return launch_dma<64, 64, 2, DmaDgradOpF>(a, npix, g.C, stream,
-                                             conv_cost(g, g.C, sizeof(T), false), "conv_dgrad");
+    const Cost cost = conv_cost(g, g.C, sizeof(T), false);
+    return f32_dma_runs(g.C, npix)
+               ? launch_dma<64, 64, 2, DmaDgradOpRuns>(a, npix, g.C, stream, cost, "conv_dgrad")
+               : launch_dma<64, 64, 2, DmaDgradOpF>(a, npix, g.C, stream, cost, "conv_dgrad");
   }
   Plan p = plan_tiles(g.C, (int)npix, ns, ws != nullptr);
   if (p.splits > 1 && (size_t)p.splits * npix * g.C > ws_floats) {

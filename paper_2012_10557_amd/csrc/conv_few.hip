@@ -22,6 +22,8 @@
 // 256 at 14 x 14, 4 frames 17.2 -> 5.9, 36 frames 33.2 -> 22.3; 128 at
 // 28 x 28, 4 frames 15.2 -> 5.9, 16 frames 22.1 -> 14.0.  fp32: 64 channels at
 // 16 x 16, 48 frames 23.0 -> 15.0 us; 256 at 14 x 14, 16 frames 60.8 -> 48.6.
+// fp32 sums are kept in runs (RunSum), which costs 1 to 2.5% (16 fp32 frames
+// at 224 px 920 -> 930 us per call).
 #include "kernels.hpp"
 
 namespace ekya {
@@ -50,51 +52,6 @@ struct FewArgs {
   void* y;
   ConvEpilogue epi;
   int tiles_m, tiles_n;
-};
-
-// acc += products, stage by stage.  A long chain of fp32 products in one
-// accumulator rounds worse than the shorter chains of split tiles, so fp32
-// products go to accumulators of their own, added to acc every RUN stages (32
-// products each).  Relative error against float64 (split tiles, one chain, RUN
-// 8, 4, 2): 256 channels at 14 x 14, 16 frames 2.5e-7, 4.2e-7, 2.0e-7, 1.6e-7,
-// 1.3e-7; 128 at 8 x 8, 48 frames 1.55e-7, 2.1e-7, 1.9e-7, 1.47e-7, 1.2e-7:
-// 4 is the longest that is nowhere further off than the split tiles.  It costs
-// 1 to 2.5% (16 fp32 frames at 224 px 920 -> 930 us per call).
-constexpr int RUN = 4;
-template <typename T, int TI, int TJ> struct RunSum {
-  f32x4 (&acc)[TI][TJ];
-  f32x4 part[TI][TJ];
-  int n = 0;
-  __device__ __forceinline__ RunSum(f32x4 (&a)[TI][TJ]) : acc(a) { clear(); }
-  __device__ __forceinline__ void clear() {
-    if constexpr (sizeof(T) == 4) {
-#pragma unroll
-      for (int i = 0; i < TI; ++i)
-#pragma unroll
-        for (int j = 0; j < TJ; ++j) part[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
-    }
-  }
-  __device__ __forceinline__ void add(const uint4 (&a)[TI], const uint4 (&b)[TJ]) {
-    if constexpr (sizeof(T) == 4)
-      mma_tile(part, a, b, (T*)nullptr);
-    else
-      mma_tile(acc, a, b, (T*)nullptr);
-  }
-  __device__ __forceinline__ void flush() {
-    if constexpr (sizeof(T) == 4) {
-#pragma unroll
-      for (int i = 0; i < TI; ++i)
-#pragma unroll
-        for (int j = 0; j < TJ; ++j) acc[i][j] += part[i][j];
-    }
-  }
-  __device__ __forceinline__ void end_stage() {
-    if (sizeof(T) == 4 && ++n == RUN) {
-      flush();
-      clear();
-      n = 0;
-    }
-  }
 };
 
 // Sum of the partial tiles in order, then the epilogue.
@@ -212,7 +169,7 @@ __global__ __launch_bounds__(NW * 64) void conv_few_kernel(FewArgs a) {
     if (s0 + p < s1) issue(s0 + p, ring + p * SU);
   const int off[2] = {fr * 8 + (q ^ (fr & 7)), fr * 8 + ((4 + q) ^ (fr & 7))};
   uint4* slot = ring;
-  RunSum<T, TI, TJ> sum(acc);
+  RunSum<T, TI, TJ, FP32_RUN> sum(acc);
   for (int st = s0; st < s1; ++st) {
     // stages st + 1 .. st + NB - 1 may still be in flight
     if (st + NB - 1 < s1)
@@ -317,7 +274,7 @@ __global__ __launch_bounds__(NG * (TM / 32) * (TN / 32) * 64) void conv_few_shar
     if (p < count) issue(s0 + p, ring + p * SU);
   const int off[2] = {fr * 8 + (q ^ (fr & 7)), fr * 8 + ((4 + q) ^ (fr & 7))};
   int slot = 0;
-  RunSum<T, 2, 2> sum(acc);
+  RunSum<T, 2, 2, FP32_RUN> sum(acc);
   for (int it = 0; it < rounds; ++it) {
     // the wave's copies of stage `it` have landed (later ones may be in flight)
     if (it + NB - 2 < count)

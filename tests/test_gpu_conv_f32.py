@@ -34,3 +34,30 @@ def test_f32_convolution_matches_float64(N, H, W, C, K, R, stride):
     ref = conv2d_input(xd.shape, wd, dyd, stride, R // 2).permute(0, 2, 3, 1)
     mag = conv2d_input(xd.shape, wd.abs(), dyd.abs(), stride, R // 2).permute(0, 2, 3, 1)
     assert ((dx - ref).abs() <= K * R * R * 2.0 ** -24 * mag + 1e-30).all()
+
+
+# relative error against float64 of register-staged tiles whose reduction is
+# split in two or three, measured at the same shapes: forward, data gradient
+SPLIT = [(10, 56, 64, 2.10e-7, 3.05e-7), (20, 28, 128, 2.54e-7, 3.51e-7), (40, 14, 256, 3.51e-7, 4.90e-7),
+         (75, 7, 512, 4.80e-7, 6.80e-7)]
+
+
+@pytest.mark.parametrize("N,H,C,fwd,dgrad", SPLIT)
+def test_f32_sums_round_no_worse_than_split_tiles(N, H, C, fwd, dgrad):
+    """At 449 to 511 tiles a split reduction would fill the chip; one chain of
+    n products instead has 1.4 to 1.7 times its rounding error."""
+    import torch
+    import torch.nn.functional as F
+    from torch.nn.grad import conv2d_input
+    from paper_2012_10557_amd import binding
+    gen = torch.Generator().manual_seed(C)
+    x, w = torch.randn(N, H, H, C, generator=gen).relu(), torch.randn(C, C, 3, 3, generator=gen)
+    dy = torch.randn(N, H, H, C, generator=gen)
+    y = binding.ekya_op_conv2d(x.cuda(), w.cuda(), 1, 1)[:8].cpu().double()
+    dx = binding.ekya_op_conv2d_dgrad(dy.cuda(), w.cuda(), (N, H, H, C), 1, 1)[:8].cpu().double()
+    xd, dyd = (v[:8].double().permute(0, 3, 1, 2) for v in (x, dy))
+    ref = F.conv2d(xd, w.double(), padding=1).permute(0, 2, 3, 1)
+    rdx = conv2d_input(xd.shape, w.double(), dyd, 1, 1).permute(0, 2, 3, 1)
+    err = [((a - b).norm() / b.norm()).item() for a, b in ((y, ref), (dx, rdx))]
+    print(" ".join(f"{e:.2e}" for e in err))
+    assert err[0] <= fwd and err[1] <= dgrad
