@@ -2903,6 +2903,9 @@ bool f32_dma_ok(int rows, long long cols, int red_channels, long long image_elem
   return red_channels % 32 == 0 && image_elems < (1LL << 31) &&
          cdiv(rows, 64) * cdivl(cols, 64) > 448;
 }
+// The copies fetch 16-byte units; the register-staged tiles' loads need 4-byte
+// alignment only, and take a layer call's tensors that start elsewhere.
+bool lds_copy_ok(const void* p) { return reinterpret_cast<uintptr_t>(p) % 16 == 0; }
 // Below kTargetBlocks tiles, where the register-staged tiles would split the
 // reduction, its sums are kept in runs (RunSum): one chain of 2304 products
 // rounds to 5.9e-7 against float64, its split in three to 3.5e-7, runs to
@@ -3129,9 +3132,9 @@ hipError_t conv_fwd_t(const ConvGeom& g, const void* x, const void* w, void* y,
     }
     return e;
   }
-  if (sizeof(T) == 4 && conv_few_ok(DT_F32, g))
-    return conv_few_fwd(DT_F32, g, x, w, y, epi, stream);
-  if (sizeof(T) == 4 &&
+  const bool direct = sizeof(T) == 4 && lds_copy_ok(x);
+  if (direct && conv_few_ok(DT_F32, g)) return conv_few_fwd(DT_F32, g, x, w, y, epi, stream);
+  if (direct &&
       f32_dma_ok(g.K, (long long)g.N * g.P * g.Q, g.C, (long long)g.H * g.W * g.C)) {
     DmaFwdArgsT<float> a{g, (const float*)x, (const float*)w, (float*)y, epi,
                          SplitOut{nullptr, 1, g.R * g.S * g.C / 32}, 0, 0};
@@ -3176,7 +3179,8 @@ hipError_t conv_dgrad_t(const ConvGeom& g, const void* dy, const void* wt, void*
   if (sizeof(T) == 2) return conv_dgrad_dma(g, dy, wt, dx, res, ws, ws_floats, stream, sink);
   const int ns = cdiv(g.R * g.S * g.K, KU_MAIN * E);
   const long long npix = (long long)g.N * g.H * g.W;
-  if (sizeof(T) == 4 && f32_dma_ok(g.C, npix, g.K, (long long)g.P * g.Q * g.K)) {
+  if (sizeof(T) == 4 && lds_copy_ok(dy) &&
+      f32_dma_ok(g.C, npix, g.K, (long long)g.P * g.Q * g.K)) {
     DmaDgradArgsT<float> a{g, (const float*)dy, (const float*)wt, (float*)dx, (const float*)res,
                            SplitOut{nullptr, 1, ns}, 0, 0};
     const Cost cost = conv_cost(g, g.C, sizeof(T), false);

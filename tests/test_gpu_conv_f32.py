@@ -61,3 +61,32 @@ def test_f32_sums_round_no_worse_than_split_tiles(N, H, C, fwd, dgrad):
     err = [((a - b).norm() / b.norm()).item() for a, b in ((y, ref), (dx, rdx))]
     print(" ".join(f"{e:.2e}" for e in err))
     assert err[0] <= fwd and err[1] <= dgrad
+
+
+#        N, H, C, K, R: few output pixels, 490 tiles, 1274 tiles
+@pytest.mark.parametrize("N,H,C,K,R", [(3, 14, 64, 64, 3), (20, 28, 128, 128, 3), (52, 28, 64, 128, 1)])
+def test_tensors_aligned_to_4_bytes(N, H, C, K, R):
+    """float32 layer calls take tensors that do not start on 16 bytes: their
+    loads are not direct 16-byte copies to LDS."""
+    import torch
+    import torch.nn.functional as F
+    from torch.nn.grad import conv2d_input
+    from paper_2012_10557_amd import binding
+    gen = torch.Generator().manual_seed(N + C)
+
+    def shifted(t):
+        v = torch.zeros(t.numel() + 4, device="cuda")[1:1 + t.numel()].view(t.shape)
+        v.copy_(t)
+        assert v.data_ptr() % 16 == 4 and v.is_contiguous()
+        return v
+    x, w = torch.randn(N, H, H, C, generator=gen), torch.randn(K, C, R, R, generator=gen)
+    dy = torch.randn(N, H, H, K, generator=gen)
+    y = binding.ekya_op_conv2d(shifted(x), w.cuda(), 1, R // 2).cpu().double()
+    dx = binding.ekya_op_conv2d_dgrad(shifted(dy), w.cuda(), (N, H, H, C), 1, R // 2).cpu().double()
+    xd, wd, dyd = x.double().permute(0, 3, 1, 2), w.double(), dy.double().permute(0, 3, 1, 2)
+    ref = F.conv2d(xd, wd, padding=R // 2).permute(0, 2, 3, 1)
+    mag = F.conv2d(xd.abs(), wd.abs(), padding=R // 2).permute(0, 2, 3, 1)
+    assert ((y - ref).abs() <= C * R * R * 2.0 ** -24 * mag).all()
+    ref = conv2d_input(xd.shape, wd, dyd, 1, R // 2).permute(0, 2, 3, 1)
+    mag = conv2d_input(xd.shape, wd.abs(), dyd.abs(), 1, R // 2).permute(0, 2, 3, 1)
+    assert ((dx - ref).abs() <= K * R * R * 2.0 ** -24 * mag).all()
