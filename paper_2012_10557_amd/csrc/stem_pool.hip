@@ -11,10 +11,15 @@
 //    registers: no LDS exchange and no barrier after the input is staged;
 //  - the maximum is taken over raw sums, two rotations and one three-way
 //    maximum a value, a column tile ahead of whose maxima the next tile's MFMAs
-//    are issued, and scale, shift and ReLU are applied to pooled rows only.  Affine and ReLU are monotone in the sum once
-//    the filter rows of channels with a negative scale are negated (exact), so
-//    the result is bit for bit that of pooling the rounded stem output.
-//    Maxima skip NaNs; a window of nothing but NaNs gives -inf;
+//    are issued, and scale, shift and ReLU are applied to pooled rows only.
+//    With a finite, nonzero scale and a finite shift they are monotone in the
+//    sum once the filter rows of channels with a negative scale are negated
+//    (exact), so the result equals pooling the rounded stem output.  Any other
+//    coefficient can turn an infinite (or, times infinity, a zero) sum into a
+//    NaN, which a maximum has to skip: a wave with such a channel applies them
+//    before the maximum (in a copy of the code, as a branch in it would keep
+//    the maxima from running beside the MFMAs).  Maxima skip NaNs; a window of
+//    nothing but NaNs gives -inf;
 //  - input rows are staged in LDS once (channels 0..2 and a zero, 8 bytes a
 //    pixel), two pixels per 12-byte load where frames are 4-byte aligned and
 //    of even width (2-byte loads otherwise);
@@ -25,6 +30,8 @@
 // products, 1.3 TB/s; before, a wave per stem row finished every stem value
 // and exchanged rows through LDS, one block per CU), 500 at 112 px 206 -> 85,
 // 4 at 224 px 25.6 -> 18.0.
+#include <type_traits>
+
 #include "kernels.hpp"
 
 namespace ekya {
@@ -67,15 +74,21 @@ __device__ __forceinline__ float lane_left(float x, float before) {
       __builtin_amdgcn_update_dpp(wrapped, __float_as_int(x), 0x111, 0xF, 0xF, false));
 }
 
-// The epilogue of one pooled sum; NaN (nothing but NaNs in the window) gives
-// -inf.  Scale and shift are two roundings, as in the other convolutions'
-// epilogues.
-__device__ __forceinline__ float affine(float m, float scale, float shift, float floor) {
+// Scale and shift are two roundings, as in the other convolutions' epilogues.
+__device__ __forceinline__ float affine(float v, float scale, float shift) {
 #pragma clang fp contract(off)
-  float v = m * scale;
-  v = v + shift;
-  const float c = max_skip_nan(v, floor);
+  v = v * scale;
+  return v + shift;
+}
+// The epilogue of one pooled sum; NaN (nothing but NaNs in the window) gives
+// -inf.
+__device__ __forceinline__ float finish(float m, float scale, float shift, float floor) {
+  const float v = affine(m, scale, shift), c = max_skip_nan(v, floor);
   return v == v ? c : -INFINITY;
+}
+// Coefficients with which the affine map is monotone and keeps NaNs apart.
+__device__ __forceinline__ bool monotone(float scale, float shift) {
+  return scale != 0.f && __builtin_isfinite(scale) && __builtin_isfinite(shift);
 }
 
 // ODD: Q is odd, so the last window lacks its right column.
@@ -95,6 +108,7 @@ __global__ __launch_bounds__(SP_NT, 2) void stem_pool_kernel(StemPoolArgs a) {
   // channel's scale is negative
   uint4 fa[2][7];
   float sa[2][4], sb[2][4];  // |scale|, shift of the lane's outputs
+  bool plain = true;
 #pragma unroll
   for (int i = 0; i < 2; ++i) {
     const int k = 32 * half + 16 * i + lr, ko = 32 * half + 16 * i + 4 * kc;
@@ -110,6 +124,7 @@ __global__ __launch_bounds__(SP_NT, 2) void stem_pool_kernel(StemPoolArgs a) {
     for (int e = 0; e < 4; ++e) {
       sa[i][e] = a.epi.scale ? __builtin_fabsf(a.epi.scale[ko + e]) : 1.f;
       sb[i][e] = a.epi.shift ? a.epi.shift[ko + e] : 0.f;
+      plain = plain && monotone(sa[i][e], sb[i][e]);
     }
   }
 
@@ -164,102 +179,119 @@ __global__ __launch_bounds__(SP_NT, 2) void stem_pool_kernel(StemPoolArgs a) {
         patch[pr * PW + (c < 3 ? c : right + c - 3)] = make_uint2(0u, 0u);
     __syncthreads();
 
-    float keep[TQ][2][4];  // vertical maximum so far of each column, lane's channels
-    const int l0 = 4 * rg, pr0 = 4 * bq + 2 * rg;
-    // one stem row: f(t, i, m) gets the window maxima of tile t along the row
-    auto stem_row = [&](int l, auto&& f) {
-      const uint2* prow = patch + 2 * l * PW + 2 * lr + 2 * kc;
-      f32x4 acc[2][2];
-      auto sums = [&](int t, f32x4 (&d)[2]) {
-        uint4 fb[7];
+    // EACH: scale and shift apply to every sum, not to the pooled ones (no
+    // barrier in here: the waves of a block may differ)
+    auto rows = [&](auto EACH) {
+      float keep[TQ][2][4];  // vertical maximum so far of each column, lane's channels
+      const int l0 = 4 * rg, pr0 = 4 * bq + 2 * rg;
+      // one stem row: f(t, i, m) gets the window maxima of tile t along the row
+      auto stem_row = [&](int l, auto&& f) {
+        const uint2* prow = patch + 2 * l * PW + 2 * lr + 2 * kc;
+        f32x4 acc[2][2];
+        auto sums = [&](int t, f32x4 (&d)[2]) {
+          uint4 fb[7];
 #pragma unroll
-        for (int r = 0; r < 7; ++r) fb[r] = *reinterpret_cast<const uint4*>(prow + r * PW + 32 * t);
+          for (int r = 0; r < 7; ++r)
+            fb[r] = *reinterpret_cast<const uint4*>(prow + r * PW + 32 * t);
 #pragma unroll
-        for (int i = 0; i < 2; ++i) d[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+          for (int i = 0; i < 2; ++i) d[i] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-        for (int r = 0; r < 7; ++r)
+          for (int r = 0; r < 7; ++r)
 #pragma unroll
-          for (int i = 0; i < 2; ++i) mma_unit(d[i], fa[i][r], fb[r], (bf16*)nullptr);
-      };
-      sums(0, acc[0]);
-      float before[2][4];
+            for (int i = 0; i < 2; ++i) mma_unit(d[i], fa[i][r], fb[r], (bf16*)nullptr);
+          if constexpr (EACH.value) {
 #pragma unroll
-      for (int i = 0; i < 2; ++i)
+            for (int i = 0; i < 2; ++i)
 #pragma unroll
-        for (int e = 0; e < 4; ++e) before[i][e] = nan;
-#pragma unroll
-      for (int t = 0; t < TQ; ++t) {
-        if (t + 1 < TQ) sums(t + 1, acc[(t + 1) & 1]);  // its MFMAs run beside this tile's maxima
-        const int q = 16 * t + lr;
-#pragma unroll
-        for (int i = 0; i < 2; ++i) {
-          float m[4];
-#pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            const float v = acc[t & 1][i][e];
-            const float left = lane_left(v, before[i][e]);
-            float right = lane_right(v);  // every lane rotates, then selects
-            if (ODD) right = q + 1 < Q ? right : nan;
-            m[e] = max3_skip_nan(left, v, right);
-            before[i][e] = v;
+              for (int e = 0; e < 4; ++e) d[i][e] = affine(d[i][e], sa[i][e], sb[i][e]);
           }
-          f(t, i, m);
-        }
-      }
-    };
-    auto emit = [&](int pr, int t, int i, const float (&o)[4]) {
-      const int q = 16 * t + lr;
-      float v[4];
-#pragma unroll
-      for (int e = 0; e < 4; ++e) v[e] = affine(o[e], sa[i][e], sb[i][e], floor);
-      if (pr < PP && (lr & 1) == 0 && q < Q)
-        store4<bf16>(a.y + (((long long)n * PP + pr) * PQ + (q >> 1)) * 64 + 32 * half + 16 * i + 4 * kc,
-                     v);
-    };
-    // stem rows 2 m - 1, 2 m, 2 m + 1 of pool rows m = pr0, pr0 + 1; the last
-    // row of a window is the first of the next.  Rows outside the image count
-    // as NaNs.
-    auto clear = [&] {
-#pragma unroll
-      for (int t = 0; t < TQ; ++t)
+        };
+        sums(0, acc[0]);
+        float before[2][4];
 #pragma unroll
         for (int i = 0; i < 2; ++i)
 #pragma unroll
-          for (int e = 0; e < 4; ++e) keep[t][i][e] = nan;
-    };
-    if (p0 + l0 >= 0 && p0 + l0 < P)
-      stem_row(l0, [&](int t, int i, const float (&m)[4]) {
+          for (int e = 0; e < 4; ++e) before[i][e] = nan;
 #pragma unroll
-        for (int e = 0; e < 4; ++e) keep[t][i][e] = m[e];
-      });
-    else
-      clear();
-#pragma unroll 1
-    for (int j = 0; j < 2; ++j) {
-      const int l = l0 + 2 * j, pr = pr0 + j;
-      if (p0 + l + 1 < P)
-        stem_row(l + 1, [&](int t, int i, const float (&m)[4]) {
+        for (int t = 0; t < TQ; ++t) {
+          if (t + 1 < TQ) sums(t + 1, acc[(t + 1) & 1]);  // its MFMAs run beside this tile's maxima
+          const int q = 16 * t + lr;
 #pragma unroll
-          for (int e = 0; e < 4; ++e) keep[t][i][e] = max_skip_nan(keep[t][i][e], m[e]);
-        });
-      if (p0 + l + 2 < P) {
-        stem_row(l + 2, [&](int t, int i, const float (&m)[4]) {
-          float o[4];
+          for (int i = 0; i < 2; ++i) {
+            float m[4];
 #pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            o[e] = max_skip_nan(keep[t][i][e], m[e]);
-            keep[t][i][e] = m[e];
+            for (int e = 0; e < 4; ++e) {
+              const float v = acc[t & 1][i][e];
+              const float left = lane_left(v, before[i][e]);
+              float right = lane_right(v);  // every lane rotates, then selects
+              if (ODD) right = q + 1 < Q ? right : nan;
+              m[e] = max3_skip_nan(left, v, right);
+              before[i][e] = v;
+            }
+            f(t, i, m);
           }
-          emit(pr, t, i, o);
-        });
-      } else {
+        }
+      };
+      auto emit = [&](int pr, int t, int i, const float (&o)[4]) {
+        const int q = 16 * t + lr;
+        float v[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+          v[e] = finish(o[e], EACH.value ? 1.f : sa[i][e], EACH.value ? 0.f : sb[i][e], floor);
+        if (pr < PP && (lr & 1) == 0 && q < Q)
+          store4<bf16>(a.y + (((long long)n * PP + pr) * PQ + (q >> 1)) * 64 + 32 * half + 16 * i +
+                           4 * kc,
+                       v);
+      };
+      // stem rows 2 m - 1, 2 m, 2 m + 1 of pool rows m = pr0, pr0 + 1; the last
+      // row of a window is the first of the next.  Rows outside the image count
+      // as NaNs.
+      auto clear = [&] {
 #pragma unroll
         for (int t = 0; t < TQ; ++t)
 #pragma unroll
-          for (int i = 0; i < 2; ++i) emit(pr, t, i, keep[t][i]);
+          for (int i = 0; i < 2; ++i)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) keep[t][i][e] = nan;
+      };
+      if (p0 + l0 >= 0 && p0 + l0 < P)
+        stem_row(l0, [&](int t, int i, const float (&m)[4]) {
+#pragma unroll
+          for (int e = 0; e < 4; ++e) keep[t][i][e] = m[e];
+        });
+      else
         clear();
+#pragma unroll 1
+      for (int j = 0; j < 2; ++j) {
+        const int l = l0 + 2 * j, pr = pr0 + j;
+        if (p0 + l + 1 < P)
+          stem_row(l + 1, [&](int t, int i, const float (&m)[4]) {
+#pragma unroll
+            for (int e = 0; e < 4; ++e) keep[t][i][e] = max_skip_nan(keep[t][i][e], m[e]);
+          });
+        if (p0 + l + 2 < P) {
+          stem_row(l + 2, [&](int t, int i, const float (&m)[4]) {
+            float o[4];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+              o[e] = max_skip_nan(keep[t][i][e], m[e]);
+              keep[t][i][e] = m[e];
+            }
+            emit(pr, t, i, o);
+          });
+        } else {
+#pragma unroll
+          for (int t = 0; t < TQ; ++t)
+#pragma unroll
+            for (int i = 0; i < 2; ++i) emit(pr, t, i, keep[t][i]);
+          clear();
+        }
       }
-    }
+    };
+    if (__builtin_expect(__all(plain), 1))
+      rows(std::false_type{});
+    else
+      rows(std::true_type{});
   }
 }
 

@@ -44,3 +44,30 @@ def test_first_classifier_update_matches_oracle(H, W):
     err = np.linalg.norm(a - b) / np.linalg.norm(b - z)
     print(f"{H} x {W}: {err:.2e}")
     assert err <= 2e-2
+
+
+@pytest.mark.parametrize("px", [32, 64, 144, 224])
+def test_zero_scale_channels_skip_infinite_sums(px):
+    """A BatchNorm scale of 0 makes a finite sum the shift and an infinite one
+    NaN, which the pool's maximum skips: with every scale 0 and one infinite
+    pixel in the last corner (each window that sees it holds finite sums too)
+    the frames are classified as they are without it, here by the classifier's
+    bias.  A pooled -inf would make every logit NaN."""
+    import torch
+    from paper_2012_10557_amd import binding
+    net = ResNet18(6)
+    named = net.unpack(kaiming_resnet18_weights(seed=1))
+    named["bn1.weight"][:] = 0.0
+    named["bn1.bias"][:] = np.random.default_rng(px).uniform(0.1, 1.0, 64)
+    named["fc.weight"][:] *= 1e-3
+    named["fc.bias"][:] = [0, 0, 0, 0, 1, 0]
+    w = torch.tensor(net.pack(named), dtype=torch.float32, device="cuda")
+    frames = torch.randn(3, px, px, 3, generator=torch.Generator().manual_seed(px)).to(torch.bfloat16)
+    frames[0, -1, -1, 0] = float("inf")
+    frames[1, -1, -1, 1] = float("-inf")
+    ctx = binding.ekya_create(0, 6)
+    try:
+        labels = binding.ekya_infer(ctx, w, frames.cuda(), px)
+    finally:
+        binding.ekya_destroy(ctx)
+    assert labels.tolist() == [4, 4, 4]
