@@ -1384,8 +1384,9 @@ __global__ __launch_bounds__(256) void softmax_ce_kernel(const float* z, const i
 // so no intermediate dz array or extra launch is needed.
 template <typename T, int NW, int IMAX>
 __global__ __launch_bounds__(NW * 64) void head_fwd_kernel(const T* x, int HW, const float* fin,
-                                                           const float* W, const float* b, int I,
-                                                           int J, float* pooled, float* z) {
+                                                           const int32_t* rows, const float* W,
+                                                           const float* b, int I, int J,
+                                                           float* pooled, float* z) {
   constexpr int E = Elt<T>::E;
   __shared__ float fl[IMAX];
   __shared__ float red[NW][8];
@@ -1431,7 +1432,8 @@ __global__ __launch_bounds__(NW * 64) void head_fwd_kernel(const T* x, int HW, c
       fl[i] = v;
     }
   } else {
-    for (int i = t; i < I; i += NW * 64) fl[i] = fin[(long long)n * I + i];
+    const float* fr = fin + (long long)(rows ? rows[n] : n) * I;
+    for (int i = t; i < I; i += NW * 64) fl[i] = fr[i];
   }
   __syncthreads();
   for (int j0 = 0; j0 < J; j0 += 8) {
@@ -1520,12 +1522,14 @@ struct HeadBnArgs {
   float* part;
 };
 
-template <typename T, bool BNP>
+// ROWS: sample n's features are row rows[n] of f.
+template <typename T, bool BNP, bool ROWS = false>
 __global__ __launch_bounds__(256) void head_bwd_kernel(const float* z, const int32_t* labels,
                                                        const int32_t* idx, int N, int J,
-                                                       const float* f, const float* W, int I,
-                                                       float* dW, float* db, T* dout, int HW,
-                                                       float* out, HeadBnArgs bp, HeadSgd sgd) {
+                                                       const float* f, const int32_t* rows,
+                                                       const float* W, int I, float* dW, float* db,
+                                                       T* dout, int HW, float* out, HeadBnArgs bp,
+                                                       HeadSgd sgd) {
   constexpr int E = Elt<T>::E;
   const int t = threadIdx.x;
   // a gradient element, or with `sgd` its momentum step (as sgd_ranges_kernel)
@@ -1540,7 +1544,7 @@ __global__ __launch_bounds__(256) void head_bwd_kernel(const float* z, const int
   };
   __shared__ float rdz[256][HEAD_JMAX];
   __shared__ float rl[256];
-  __shared__ int rc[256], rb[256];
+  __shared__ int rc[256], rb[256], rf[ROWS ? 256 : 1];
   float dz[HEAD_JMAX];
   if (blockIdx.x < (unsigned)HEAD_WB) {
     // features i = 64 b + t % 64; samples of each 256-row chunk in 4 slices,
@@ -1565,6 +1569,7 @@ __global__ __launch_bounds__(256) void head_bwd_kernel(const float* z, const int
         rl[t] = l;
         rc[t] = c;
         rb[t] = (!ok || !isfinite(l)) ? 1 : 0;
+        if (ROWS) rf[t] = rows[n0 + t];
       }
       __syncthreads();
       const int per = (cnt + 3) / 4;
@@ -1573,7 +1578,9 @@ __global__ __launch_bounds__(256) void head_bwd_kernel(const float* z, const int
         float fv[8];
 #pragma unroll
         for (int q = 0; q < 8; ++q)
-          fv[q] = (k + q < k1 && i < I) ? f[(long long)(n0 + k + q) * I + i] : 0.f;
+          fv[q] = (k + q < k1 && i < I)
+                      ? f[(long long)(ROWS ? rf[k + q] : n0 + k + q) * I + i]
+                      : 0.f;
 #pragma unroll
         for (int q = 0; q < 8; ++q)
           if (k + q < k1)
@@ -2312,7 +2319,7 @@ hipError_t softmax_ce(const float* z, const int32_t* labels, const int32_t* idx,
 
 hipError_t head_forward(int dt, const void* x, int HW, const float* f, const float* W,
                         const float* b, int N, int I, int J, float* pooled, float* z,
-                        hipStream_t stream) {
+                        hipStream_t stream, const int32_t* rows) {
   if (N == 0) return hipSuccess;
   if (I > 2048 || I % dtype_vec(dt) != 0) return hipErrorInvalidValue;
   TimedLaunch tl(stream);
@@ -2320,10 +2327,10 @@ hipError_t head_forward(int dt, const void* x, int HW, const float* f, const flo
     using T = std::remove_pointer_t<decltype(tp)>;
     if (I <= 512)  // ResNet18's 512 features: 16 waves per sample
       hipLaunchKernelGGL((head_fwd_kernel<T, 16, 512>), dim3(N), dim3(1024), 0, stream,
-                         (const T*)x, HW, f, W, b, I, J, pooled, z);
+                         (const T*)x, HW, f, rows, W, b, I, J, pooled, z);
     else
       hipLaunchKernelGGL((head_fwd_kernel<T, 4, 2048>), dim3(N), dim3(256), 0, stream,
-                         (const T*)x, HW, f, W, b, I, J, pooled, z);
+                         (const T*)x, HW, f, rows, W, b, I, J, pooled, z);
   }), "head_fwd", x ? (double)N * HW * I * dtype_size(dt) : (double)N * I * 4);
 }
 
@@ -2332,9 +2339,10 @@ bool head_backward_fused(int J, int I) { return J <= HEAD_JMAX && I <= 64 * HEAD
 hipError_t head_backward(int dt, const float* z, const int32_t* labels, const int32_t* idx, int N,
                          int J, const float* f, const float* W, int I, float* dW, float* db,
                          void* dout, int HW, float* out, hipStream_t stream, HeadBnSink* bn,
-                         const HeadSgd* step) {
+                         const HeadSgd* step, const int32_t* rows) {
   if (bn) bn->rows = 0;
   if (step && dout) return hipErrorInvalidValue;  // dout reads W while dW's blocks would change it
+  if (rows && dout) return hipErrorInvalidValue;
   const HeadSgd sgd = step ? *step : HeadSgd{};
   if (!head_backward_fused(J, I) || I % dtype_vec(dt) != 0 || 256 % (I / dtype_vec(dt)) != 0)
     return hipErrorInvalidValue;
@@ -2352,10 +2360,14 @@ hipError_t head_backward(int dt, const float* z, const int32_t* labels, const in
     using T = std::remove_pointer_t<decltype(tp)>;
     if (bnp)
       hipLaunchKernelGGL((head_bwd_kernel<T, true>), dim3(HEAD_WB + dblocks), dim3(256), 0, stream,
-                         z, labels, idx, N, J, f, W, I, dW, db, (T*)dout, HW, out, ha, sgd);
+                         z, labels, idx, N, J, f, rows, W, I, dW, db, (T*)dout, HW, out, ha, sgd);
+    else if (rows)
+      hipLaunchKernelGGL((head_bwd_kernel<T, false, true>), dim3(HEAD_WB), dim3(256), 0, stream, z,
+                         labels, idx, N, J, f, rows, W, I, dW, db, (T*)dout, HW, out, ha, sgd);
     else
       hipLaunchKernelGGL((head_bwd_kernel<T, false>), dim3(HEAD_WB + dblocks), dim3(256), 0,
-                         stream, z, labels, idx, N, J, f, W, I, dW, db, (T*)dout, HW, out, ha, sgd);
+                         stream, z, labels, idx, N, J, f, rows, W, I, dW, db, (T*)dout, HW, out,
+                         ha, sgd);
   }), "head_bwd", (double)Mr * I * dtype_size(dt) * (bnp ? 3 : 1) + (double)N * I * 4);
   if (e == hipSuccess && bnp) bn->rows = 64;
   return e;

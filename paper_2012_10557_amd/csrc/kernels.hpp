@@ -246,9 +246,10 @@ hipError_t avgpool_bwd(int dt, const float* df, int N, int HW, int C, void* dx,
                        hipStream_t stream);
 
 // --------------------------------------------------------------- classifier
-// z[N, J] = f[N, I] W[J, I]^T + b, then max(., 0) if relu
+// z[N, J] = f[N, I] W[J, I]^T + b, then max(., 0) if relu.  Here and below,
+// row n of f is at f[rows[n]] with `rows`.
 hipError_t fc_fwd(const float* f, const float* Wt, const float* b, int N, int I, int J, float* z,
-                  hipStream_t stream, bool relu = false);
+                  hipStream_t stream, bool relu = false, const int32_t* rows = nullptr);
 // Softmax cross-entropy over rows of z[N, J] with labels (selected through
 // `idx` when non-null): dz = (softmax - onehot)/N, out[0] = mean loss,
 // out[1] = correct count (as float), out[2] = non-finite flag.
@@ -258,7 +259,8 @@ hipError_t softmax_ce(const float* z, const int32_t* labels, const int32_t* idx,
 // mask [N, I], df is zero where mask is not positive (backward through a ReLU
 // whose output is mask).
 hipError_t fc_bwd(const float* dz, const float* f, const float* Wt, int N, int I, int J, float* dW,
-                  float* db, float* df, hipStream_t stream, const float* mask = nullptr);
+                  float* db, float* df, hipStream_t stream, const float* mask = nullptr,
+                  const int32_t* rows = nullptr);
 // Fused classifier head.  Forward: pooled[N, I] (fp32) = mean over HW pixels
 // of x[N, HW, I] (x null: features f are used and pooled is not written),
 // z = pooled W^T + b (J = 0: the pooled features only).  Backward (J <= 16, I <= 512; head_backward_fused):
@@ -267,7 +269,7 @@ hipError_t fc_bwd(const float* dz, const float* f, const float* Wt, int N, int I
 // is non-null, dout[N, HW, I] = (dz W) / HW.
 hipError_t head_forward(int dt, const void* x, int HW, const float* f, const float* W,
                         const float* b, int N, int I, int J, float* pooled, float* z,
-                        hipStream_t stream);
+                        hipStream_t stream, const int32_t* rows = nullptr);
 // bn (with dout): the BatchNorm whose output (ReLU mask ymask, input z,
 // batch mean) dout is the gradient of; when the fused path can, the launch
 // also leaves that BatchNorm's backward chunk partials in bn->part and sets
@@ -281,7 +283,7 @@ struct HeadBnSink {
 };
 bool head_backward_fused(int J, int I);
 // step (without dout): in place of dW and db, the momentum step of the
-// classifier itself, v = mu v + g, w = w - lr v.
+// classifier itself, v = mu v + g, w = w - lr v.  rows: without dout only.
 struct HeadSgd {
   float *w = nullptr, *wv = nullptr, *b = nullptr, *bv = nullptr;
   float lr = 0.f, mu = 0.f;
@@ -290,7 +292,7 @@ hipError_t head_backward(int dt, const float* z, const int32_t* labels, const in
                          int J, const float* f, const float* W, int I, float* dW, float* db,
                          void* dout, int HW, float* out, hipStream_t stream,
                          HeadBnSink* bn = nullptr,
-                         const HeadSgd* step = nullptr);
+                         const HeadSgd* step = nullptr, const int32_t* rows = nullptr);
 // Count of rows whose argmax matches the label, accumulated into *count.
 hipError_t count_correct(const float* z, const int32_t* labels, int N, int J, int32_t* count,
                          hipStream_t stream);

@@ -34,14 +34,16 @@ struct LinArgs {
   const float* bias;   // [N] or null
   const float* mask;   // [M][N] or null: the result passes where mask > 0
   int relu;            // max(., 0)
+  const int32_t* rows; // null, or row m of A (AK) / row k of B (BROWS) is at rows[.]
   float* C;            // [M][N]
   float* rowsum;       // [M] or null: sum_k A(m, k) (k-strided A)
 };
 
-// Elements k .. k + 3 of operand row `row`; zero from `end` on.
-template <bool KC>
+// Elements k .. k + 3 of operand row `row`; zero from `end` on.  ROWS (k-strided
+// operands): element k is at rows[k] * ld.
+template <bool KC, bool ROWS = false>
 __device__ __forceinline__ f32x4 lin_load(const float* P, long long ld, int row, int k, int end,
-                                          int vec) {
+                                          int vec, const int32_t* rows = nullptr) {
   f32x4 v = {0.f, 0.f, 0.f, 0.f};
   if constexpr (KC) {
     const float* p = P + row * ld + k;
@@ -52,6 +54,10 @@ __device__ __forceinline__ f32x4 lin_load(const float* P, long long ld, int row,
       for (int e = 0; e < 4; ++e)
         if (k + e < end) v[e] = p[e];
     }
+  } else if constexpr (ROWS) {
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+      if (k + e < end) v[e] = P[rows[k + e] * ld + row];
   } else {
     const float* p = P + (long long)k * ld + row;
 #pragma unroll
@@ -61,7 +67,7 @@ __device__ __forceinline__ f32x4 lin_load(const float* P, long long ld, int row,
   return v;
 }
 
-template <bool AK, bool BK, int T>
+template <bool AK, bool BK, int T, bool BROWS>
 __global__ __launch_bounds__(256) void linear_kernel(LinArgs a) {
   constexpr int S = 16 * T;           // tile side
   constexpr int NA = T == 1 ? 8 : 4;  // accumulators per 16 x 16 tile
@@ -75,6 +81,8 @@ __global__ __launch_bounds__(256) void linear_kernel(LinArgs a) {
 #pragma unroll
   for (int i = 0; i < T; ++i) {
     ra[i] = min(m0 + 16 * i + r, a.M - 1);
+    if constexpr (AK && BK)
+      if (a.rows) ra[i] = a.rows[ra[i]];
     rb[i] = min(n0 + 16 * i + r, a.N - 1);
   }
   const int chunks = cdiv(a.K, 16), per = cdiv(chunks, 4);
@@ -96,7 +104,7 @@ __global__ __launch_bounds__(256) void linear_kernel(LinArgs a) {
       for (int i = 0; i < T; ++i) {
         const int k = 16 * (c + u) + 4 * q;
         av[u][i] = lin_load<AK>(a.A, a.lda, ra[i], k, end, a.avec);
-        bv[u][i] = lin_load<BK>(a.B, a.ldb, rb[i], k, end, a.bvec);
+        bv[u][i] = lin_load<BK, BROWS>(a.B, a.ldb, rb[i], k, end, a.bvec, a.rows);
       }
     f32x4 acc[T][T][NA];
 #pragma unroll
@@ -171,7 +179,7 @@ int lin_vec(const float* p, long long ld, int K) {
   return reinterpret_cast<uintptr_t>(p) % 16 == 0 && ld % 4 == 0 && K % 4 == 0;
 }
 
-template <bool AK, bool BK>
+template <bool AK, bool BK, bool BROWS = false>
 hipError_t linear(LinArgs a, hipStream_t stream) {
   if (a.M < 1 || a.N < 1 || a.K < 1) return hipErrorInvalidValue;
   a.avec = AK && lin_vec(a.A, a.lda, a.K);
@@ -184,16 +192,16 @@ hipError_t linear(LinArgs a, hipStream_t stream) {
   const long long t32 = (long long)cdiv(a.M, 32) * cdiv(a.N, 32);
   if (t32 > INT_MAX) return hipErrorInvalidValue;
   if (t16 <= 512)
-    hipLaunchKernelGGL((linear_kernel<AK, BK, 1>), dim3((unsigned)t16), dim3(256), 0, stream, a);
+    hipLaunchKernelGGL((linear_kernel<AK, BK, 1, BROWS>), dim3((unsigned)t16), dim3(256), 0, stream, a);
   else
-    hipLaunchKernelGGL((linear_kernel<AK, BK, 2>), dim3((unsigned)t32), dim3(256), 0, stream, a);
+    hipLaunchKernelGGL((linear_kernel<AK, BK, 2, BROWS>), dim3((unsigned)t32), dim3(256), 0, stream, a);
   return hipGetLastError();
 }
 
 }  // namespace
 
 hipError_t fc_fwd(const float* f, const float* W, const float* b, int N, int I, int J, float* z,
-                  hipStream_t stream, bool relu) {
+                  hipStream_t stream, bool relu, const int32_t* rows) {
   if (N == 0) return hipSuccess;
   LinArgs a{};
   a.A = f;
@@ -205,12 +213,14 @@ hipError_t fc_fwd(const float* f, const float* W, const float* b, int N, int I, 
   a.K = I;
   a.bias = b;
   a.relu = relu;
+  a.rows = rows;
   a.C = z;
   return linear<true, true>(a, stream);
 }
 
 hipError_t fc_bwd(const float* dz, const float* f, const float* W, int N, int I, int J, float* dW,
-                  float* db, float* df, hipStream_t stream, const float* mask) {
+                  float* db, float* df, hipStream_t stream, const float* mask,
+                  const int32_t* rows) {
   LinArgs w{};  // dW[j][i] = sum_n dz[n][j] f[n][i]
   w.A = dz;
   w.lda = J;
@@ -221,7 +231,11 @@ hipError_t fc_bwd(const float* dz, const float* f, const float* W, int N, int I,
   w.K = N;
   w.C = dW;
   w.rowsum = db;
-  EKYA_HIP((linear<false, false>(w, stream)));
+  w.rows = rows;
+  if (rows)
+    EKYA_HIP((linear<false, false, true>(w, stream)));
+  else
+    EKYA_HIP((linear<false, false>(w, stream)));
   if (!df) return hipSuccess;
   LinArgs x{};  // df[n][i] = sum_j dz[n][j] W[j][i]
   x.A = dz;

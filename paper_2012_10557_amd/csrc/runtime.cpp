@@ -530,8 +530,8 @@ struct TrainJob {
   float *bn_mean = nullptr, *bn_invstd = nullptr, *bn_scale = nullptr, *bn_shift = nullptr;
   float* fold = nullptr;
   int32_t *d_order = nullptr, *d_fidx = nullptr;
-  void* x0 = nullptr;           // a batch's input (classifier only: an epoch's features)
-  const float* feat = nullptr;  // classifier only: the batch's features in x0
+  void* x0 = nullptr;             // a batch's input (lowest <= 4)
+  const int32_t* rows = nullptr;  // classifier only: the batch's rows of the cache
   void* stem_Z = nullptr;
   void* stem_A = nullptr;
   uint8_t* stem_arg = nullptr;
@@ -660,8 +660,7 @@ static void plan_job(Arena& a, TrainJob& j) {
   j.d_order = a.take<int32_t>((size_t)j.epochs * j.n_s);
   j.d_fidx = a.take<int32_t>((size_t)j.epochs * j.n_s);
   const long long in_elems = j.geo.stage_in_elems(net, j.lowest);
-  const size_t in_es = (j.lowest == 5) ? 4 : es;
-  j.x0 = a.take_bytes((size_t)(j.lowest == 5 ? j.n_s : j.B) * in_elems * in_es);
+  if (j.lowest <= 4) j.x0 = a.take_bytes((size_t)j.B * in_elems * es);
   j.acts.assign(net.blk.size(), BlockAct());
   if (j.lowest == 0) {
     j.stem_Z = a.take_bytes((size_t)j.B * j.geo.sh * j.geo.sw * 64 * es);
@@ -739,23 +738,23 @@ static void plan_job(Arena& a, TrainJob& j) {
 
 static inline float* bnp(float* base, const BnL& b) { return base + b.st; }
 
-// Average pool (x: layer4's output; null: the pooled features in feat) and
+// Average pool (x: layer4's output; null: the batch's rows of the cache) and
 // the classifier: pooled and logits, or with a hidden layer the pooled
 // features, the hidden layer's ReLU activations and the logits.
 static hipError_t train_head_forward(TrainJob& j, int nb, const void* x) {
   const Net& net = *j.net;
   const int hw = j.geo.lh[4] * j.geo.lw[4];
-  const float* f = x ? nullptr : j.feat;
+  const float* f = x ? nullptr : reinterpret_cast<const float*>(j.cache);
   float* pooled = x ? j.pooled : nullptr;
   if (net.hidden == 0)
     return head_forward(j.dt, x, hw, f, j.master + net.fc_w, j.master + net.fc_b, nb, 512,
-                        net.n_classes, pooled, j.logits, j.st);
+                        net.n_classes, pooled, j.logits, j.st, j.rows);
   if (x) {
     EKYA_HIP(head_forward(j.dt, x, hw, nullptr, nullptr, nullptr, nb, 512, 0, pooled, nullptr, j.st));
     f = pooled;
   }
   EKYA_HIP(fc_fwd(f, j.master + net.fc1_w, j.master + net.fc1_b, nb, 512, net.hidden, j.hid, j.st,
-                  true));
+                  true, j.rows));
   return fc_fwd(j.hid, j.master + net.fc_w, j.master + net.fc_b, nb, net.hidden, net.n_classes,
                 j.logits, j.st);
 }
@@ -867,7 +866,7 @@ static hipError_t train_backward(TrainJob& j, int nb, const int32_t* fid, float*
   const Net& net = *j.net;
   const int dt = j.dt;
   hipStream_t st = j.st;
-  const float* f = (j.lowest == 5) ? j.feat : j.pooled;
+  const float* f = (j.lowest == 5) ? reinterpret_cast<const float*>(j.cache) : j.pooled;
   void* dout = j.g[1];
   void* dnext = j.g[2];
   void* gG = j.g[3];
@@ -881,7 +880,7 @@ static hipError_t train_backward(TrainJob& j, int nb, const int32_t* fid, float*
     EKYA_HIP(fc_bwd(j.dz, j.hid, j.master + net.fc_w, nb, net.hidden, net.n_classes,
                     j.grad + net.fc_w, j.grad + net.fc_b, j.dhid, st, j.hid));
     EKYA_HIP(fc_bwd(j.dhid, f, j.master + net.fc1_w, nb, 512, net.hidden, j.grad + net.fc1_w,
-                    j.grad + net.fc1_b, j.lowest == 5 ? nullptr : j.dpooled, st));
+                    j.grad + net.fc1_b, j.lowest == 5 ? nullptr : j.dpooled, st, nullptr, j.rows));
     if (j.lowest < 5) EKYA_HIP(avgpool_bwd(dt, j.dpooled, nb, hw, 512, dout, st));
   } else if (head_backward_fused(net.n_classes, 512)) {
     // softmax cross-entropy, classifier gradients and average-pool backward
@@ -899,12 +898,12 @@ static hipError_t train_backward(TrainJob& j, int nb, const int32_t* fid, float*
     EKYA_HIP(head_backward(dt, j.logits, j.labels, fid, nb, net.n_classes, f, j.master + net.fc_w,
                            512, j.grad + net.fc_w, j.grad + net.fc_b,
                            j.lowest == 5 ? nullptr : dout, hw, ce, st, &hb,
-                           head_steps_itself(j) ? &step : nullptr));
+                           head_steps_itself(j) ? &step : nullptr, j.rows));
     head_ready = hb.rows;
   } else {
     EKYA_HIP(softmax_ce(j.logits, j.labels, fid, nb, net.n_classes, j.dz, ce, st));
     EKYA_HIP(fc_bwd(j.dz, f, j.master + net.fc_w, nb, 512, net.n_classes, j.grad + net.fc_w,
-                    j.grad + net.fc_b, j.lowest == 5 ? nullptr : j.dpooled, st));
+                    j.grad + net.fc_b, j.lowest == 5 ? nullptr : j.dpooled, st, nullptr, j.rows));
     if (j.lowest < 5) EKYA_HIP(avgpool_bwd(dt, j.dpooled, nb, hw, 512, dout, st));
   }
   if (j.lowest == 5) return hipSuccess;
@@ -1222,8 +1221,6 @@ static hipError_t job_epochs(TrainJob& j) {
   int step = 0;
   EKYA_HIP(hipEventRecord(j.ev[0], j.st));
   for (int e = 0; e < j.epochs; ++e) {
-    if (j.lowest == 5)  // 2 KB a row: the epoch's features in one launch
-      EKYA_HIP(gather_rows(j.cache, j.d_order + (size_t)e * j.n_s, j.n_s, j.row_bytes, j.x0, j.st));
     for (int b0 = 0; b0 < j.n_s; b0 += j.B) {
       const int nb = std::min(j.B, j.n_s - b0);
       const int32_t* ord = j.d_order + (size_t)e * j.n_s + b0;
@@ -1233,7 +1230,7 @@ static hipError_t job_epochs(TrainJob& j) {
         EKYA_HIP(frames_to_padded(j.dt, j.frames, fid, nb, j.geo.H, j.geo.W, net.conv[0].cin_pad,
                                   j.x0, j.st));
       else if (j.lowest == 5)
-        j.feat = reinterpret_cast<const float*>(j.x0) + (size_t)b0 * 512;
+        j.rows = ord;  // the classifier's kernels read the cache through it
       else
         EKYA_HIP(gather_rows(j.cache, ord, nb, j.row_bytes, j.x0, j.st));
       EKYA_HIP(train_forward(j, nb));

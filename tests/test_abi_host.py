@@ -119,3 +119,19 @@ def test_workspace_query_sizes():
     assert i224 > binding.ekya_infer_workspace(6, 160) > binding.ekya_infer_workspace(6, 112) > 0
     assert binding.ekya_infer_workspace(6, 31) == 0 and binding.ekya_infer_workspace(6, 224, 2) == 0
     assert binding.ekya_infer_workspace(0, 224) == 0
+
+
+@pytest.mark.parametrize("classes,hidden", [(6, 0), (20, 0), (6, 128)])
+def test_classifier_only_workspace_holds_each_feature_row_once(classes, hidden):
+    """A classifier-only job's workspace grows per frame by its cached feature
+    row (512 floats), its place in each epoch's orders, its subset index and
+    its share of the step losses: no second copy of the features, in a
+    retraining or a profiling call."""
+    from paper_2012_10557_amd import binding
+    epochs, batch, n0, n1 = 2, 64, 6400, 64000
+    row = 512 * 4 + epochs * 2 * 4 + 4 + epochs * 3 * 4 / batch
+    r = lambda n: binding.ekya_retrain_workspace(classes, 1, n, 64, 64, 40, 1.0, epochs, 0.01, 0.9, batch, hidden=hidden)
+    cfg = [{"k": 1, "subsample_frac": 1.0, "epochs": epochs, "batch": batch}]
+    p = lambda n: binding.ekya_profile_workspace(classes, cfg, n, 64, 64, 40, hidden=hidden)
+    for f in (r, p):
+        assert abs((f(n1) - f(n0)) / (n1 - n0) - row) < 1.0  # (alignment: 256 bytes a buffer)
