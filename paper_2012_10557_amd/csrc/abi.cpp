@@ -331,7 +331,7 @@ bool chan_ok(int dt, int C, bool allow3) {
 }
 
 // fp32 [K][C][R][S] weights in one of the kernels' low-precision layouts:
-// [K][RS][Cp] (crsk false) or [C][RS][K].  pack_bytes: what it takes from tmp.
+// [K][RS][Cp] (crsk false) or [C][RS][K], and what it takes from tmp.
 struct PackPlan {
   long long n;  // elements of a layout
   bool both;    // [C][RS][K] through the [K][RS][C] layouts (long filters)
@@ -421,11 +421,11 @@ ekya_status ekya_op_conv2d(int precision, const void* x, int N, int H, int W, in
   hipStream_t st = (hipStream_t)stream;
   Tmp tmp;
   int Cp = C == 3 ? ekya::dtype_vec(precision) : C;
-  const void* xp;
+  const void* xp = x;
   void* krsc;
   const ekya::ConvGeom g = make_geom(N, H, W, Cp, K, R, S, stride, pad);
   const PackPlan pp = plan_pack(precision, K, R, S, Cp, false);
-  const size_t wsf = ekya::conv_split_workspace_floats(precision, g, false);
+  const size_t wsf = ekya::conv_split_workspace_floats(precision, g, false, !ekya::lds_copy_ok(xp));
   hipError_t e = tmp.reserve({pad_bytes(precision, N, H, W, C), pp.table, pp.master, pp.out,
                               wsf * sizeof(float)});
   if (e == hipSuccess) e = pad_input(precision, x, N, H, W, C, Cp, tmp, &xp, st);
@@ -446,7 +446,7 @@ ekya_status ekya_op_conv2d_dgrad(int precision, const void* dy, const float* w, 
   void* crsk;
   const ekya::ConvGeom g = make_geom(N, H, W, C, K, R, S, stride, pad);
   const PackPlan pp = plan_pack(precision, K, R, S, C, true);
-  const size_t wsf = ekya::conv_split_workspace_floats(precision, g, true);
+  const size_t wsf = ekya::conv_split_workspace_floats(precision, g, true, !ekya::lds_copy_ok(dy));
   hipError_t e = tmp.reserve({pp.table, pp.master, pp.out, wsf * sizeof(float)});
   if (e == hipSuccess) e = pack_one(precision, w, K, C, R, S, C, true, pp, tmp, &crsk, st);
   float* ws = wsf ? tmp.get<float>(wsf) : nullptr;

@@ -2903,9 +2903,6 @@ bool f32_dma_ok(int rows, long long cols, int red_channels, long long image_elem
   return red_channels % 32 == 0 && image_elems < (1LL << 31) &&
          cdiv(rows, 64) * cdivl(cols, 64) > 448;
 }
-// The copies fetch 16-byte units; the register-staged tiles' loads need 4-byte
-// alignment only, and take a layer call's tensors that start elsewhere.
-bool lds_copy_ok(const void* p) { return reinterpret_cast<uintptr_t>(p) % 16 == 0; }
 // Below kTargetBlocks tiles, where the register-staged tiles would split the
 // reduction, its sums are kept in runs (RunSum): one chain of 2304 products
 // rounds to 5.9e-7 against float64, its split in three to 3.5e-7, runs to
@@ -3219,8 +3216,17 @@ hipEvent_t KernelTimer::take() {
 void set_thread_timer(KernelTimer* t) { t_timer = t; }
 KernelTimer* thread_timer() { return t_timer; }
 
-size_t conv_split_workspace_floats(int dt, const ConvGeom& g, bool dgrad) {
+// The copies fetch 16-byte units; the register-staged tiles' loads need 4-byte
+// alignment only, and take a layer call's tensors that start elsewhere.
+bool lds_copy_ok(const void* p) { return reinterpret_cast<uintptr_t>(p) % 16 == 0; }
+
+size_t conv_split_workspace_floats(int dt, const ConvGeom& g, bool dgrad, bool general) {
   const int E = dtype_vec(dt);
+  if (!general && !dgrad && conv_few_ok(dt, g)) return 0;
+  if (!general && dt == DT_F32 &&
+      (dgrad ? f32_dma_ok(g.C, (long long)g.N * g.H * g.W, g.K, (long long)g.P * g.Q * g.K)
+             : f32_dma_ok(g.K, (long long)g.N * g.P * g.Q, g.C, (long long)g.H * g.W * g.C)))
+    return 0;
   if (dt == DT_BF16 && dgrad) {
     const long long npix = (long long)g.N * g.H * g.W;
     const DmaPlan p = g.stride == 2 && g.R * g.S > 1 ? plan_dgrad_s2(g, true)

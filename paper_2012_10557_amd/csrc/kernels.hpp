@@ -116,7 +116,11 @@ hipError_t stem_pool_fwd(int dt, const ConvGeom& g, const void* frames, const in
 hipError_t conv_dgrad(int dt, const ConvGeom& g, const void* dy, const void* w_crsk, void* dx,
                       const void* res, float* ws, size_t ws_floats, hipStream_t stream,
                       BnStatsSink* sink = nullptr);
-size_t conv_split_workspace_floats(int dt, const ConvGeom& g, bool dgrad);
+// general: also for calls that the one-launch kernels do not take (a BatchNorm
+// sink, fp32 activations that do not start on 16 bytes).
+size_t conv_split_workspace_floats(int dt, const ConvGeom& g, bool dgrad, bool general);
+// Whether fp32 activations at p may go to LDS by 16-byte copies.
+bool lds_copy_ok(const void* p);
 // The bf16 data gradient of a 3x3 / stride-2 / pad-1 convolution g plus that
 // of a 1x1 / stride-2 / pad-0 convolution gs on the same input (a projection
 // shortcut; dy_sc its output gradient, wt_sc its weights [C][1][1][K2]) in

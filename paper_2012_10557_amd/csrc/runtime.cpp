@@ -347,6 +347,12 @@ struct EvalBufs {
 
 static ConvGeom conv_geom(const Net& net, const Geo& g, int ci, int n);
 
+// Whether the eval-mode stem reads 3-channel frames itself (no padded copy of
+// them), for any number of frames.
+static bool stem_reads_frames(const Net& net, const Geo& g) {
+  return stem_pool_ok(net.dt, conv_geom(net, g, 0, 1));
+}
+
 // Kinds of memoised scratch sizes (PlanMemo).
 enum ScratchKind { kScratchEval, kScratchTrain, kScratchWgrad, kScratchBn };
 
@@ -379,7 +385,8 @@ static void plan_eval(Arena& a, const Net& net, const Geo& g, int lo, int hi, in
     for (size_t i = 0; i < net.conv.size(); ++i)
       if (net.conv[i].stage >= lo && net.conv[i].stage <= hi)
         for (int n = 1; n <= cap; ++n)
-          ws = std::max(ws, conv_split_workspace_floats(net.dt, conv_geom(net, g, (int)i, n), false));
+          ws = std::max(ws, conv_split_workspace_floats(net.dt, conv_geom(net, g, (int)i, n), false,
+                                                        false));
     return ws;
   });
   b.ws = a.take<float>(b.ws_floats);
@@ -608,8 +615,9 @@ static size_t ws_floats(const TrainJob& j) {  // (the memo's kScratchTrain)
       // the last weight gradients of a step run on the main stream in ws
       if (fused_update(net, c)) m = std::max(m, conv_wgrad_partials_floats(j.dt, cg));
       m = std::max(m, bn_partials_floats((long long)n * cg.P * cg.Q, c.cout));
-      m = std::max(m, conv_split_workspace_floats(j.dt, cg, false));
-      if (c.stage > 0) m = std::max(m, conv_split_workspace_floats(j.dt, cg, true));
+      // (bf16 convolutions of a training step have a BatchNorm sink)
+      m = std::max(m, conv_split_workspace_floats(j.dt, cg, false, j.dt == DT_BF16));
+      if (c.stage > 0) m = std::max(m, conv_split_workspace_floats(j.dt, cg, true, false));
     }
   }
   return std::max<size_t>(m, 16);
@@ -733,7 +741,8 @@ static void plan_job(Arena& a, TrainJob& j) {
   }
   j.eval_cap = std::max(1, std::min(j.n_h, cap));
   plan_eval(a, net, j.geo, j.lowest, 5, j.eval_cap, j.eval);
-  if (j.lowest == 0) j.eval_in = a.take_bytes((size_t)j.eval_cap * in_elems * es);
+  if (j.lowest == 0 && !stem_reads_frames(net, j.geo))
+    j.eval_in = a.take_bytes((size_t)j.eval_cap * in_elems * es);
 }
 
 static inline float* bnp(float* base, const BnL& b) { return base + b.st; }
@@ -1166,7 +1175,7 @@ static hipError_t build_cache(const Net& net, const Geo& g, const void* shadow, 
     const int cnt = std::min(per, n - i0);
     const void* src = d_idx ? frames : reinterpret_cast<const char*>(frames) + i0 * fbytes;
     void* out = reinterpret_cast<char*>(cache) + (row0 + i0) * row_bytes;
-    if (stem_pool_ok(net.dt, conv_geom(net, g, 0, cnt))) {  // the stem reads the frames
+    if (stem_reads_frames(net, g)) {  // the stem reads the frames
       EKYA_HIP(eval_forward(net, g, shadow, fold, master, 0, lowest - 1, src, cnt, eb, out, st,
                             d_idx ? d_idx + i0 : nullptr));
       continue;
@@ -1274,7 +1283,7 @@ static hipError_t job_epochs(TrainJob& j) {
       const void* in;
       if (j.lowest == 0) {
         in = reinterpret_cast<const char*>(j.hframes) + h0 * fbytes;
-        if (!stem_pool_ok(j.dt, conv_geom(net, j.geo, 0, cnt))) {
+        if (!stem_reads_frames(net, j.geo)) {
           EKYA_HIP(frames_to_padded(j.dt, in, nullptr, cnt, j.geo.H, j.geo.W, net.conv[0].cin_pad,
                                     j.eval_in, qe));
           in = j.eval_in;
@@ -1420,8 +1429,9 @@ static void plan_retrain(Arena& a, TrainJob& j, RetrainBufs& r) {
   if (j.lowest >= 1) {
     r.cache = a.take_bytes((size_t)(j.n_s + j.n_h) * j.row_bytes);
     r.d_S = a.take<int32_t>(j.n_s);
-    r.padded = a.take_bytes((size_t)kCacheChunk * j.geo.H * j.geo.W * net.conv[0].cin_pad *
-                            dtype_size(j.dt));
+    if (!stem_reads_frames(net, j.geo))
+      r.padded = a.take_bytes((size_t)kCacheChunk * j.geo.H * j.geo.W * net.conv[0].cin_pad *
+                              dtype_size(j.dt));
     plan_eval(a, net, j.geo, 0, j.lowest - 1, kCacheChunk, r.ceb);
   }
 }
@@ -1610,7 +1620,8 @@ static void plan_profile(Arena& a, ProfilePlan& pp, int n_heldout, int H, int W)
   for (auto& j : pp.jobs) plan_job(a, j);
   for (auto& ci : pp.caches) ci.p = a.take_bytes((size_t)(ci.n_rows_s + n_heldout) * ci.row_bytes);
   pp.d_S = a.take<int32_t>(std::max(1, pp.n_max));
-  pp.padded = a.take_bytes((size_t)kCacheChunk * H * W * net.conv[0].cin_pad * es);
+  if (!stem_reads_frames(net, geo))
+    pp.padded = a.take_bytes((size_t)kCacheChunk * H * W * net.conv[0].cin_pad * es);
   plan_eval(a, net, geo, 0, 4, kCacheChunk, pp.ceb);
   pp.pmaster = a.take<float>(net.total);
   pp.pfold = a.take<float>(2 * net.bn_channels);
@@ -1815,7 +1826,9 @@ static void plan_infer(Arena& a, const Net& net, const Geo& geo, int resolution,
     b.fold = a.take<float>(2 * net.bn_channels);
     b.shadow = a.take_bytes(net.shadow_elems * es);
   }
-  b.padded = a.take_bytes((size_t)kInferChunk * resolution * resolution * net.conv[0].cin_pad * es);
+  // resized frames where the stem reads frames, else its padded input
+  const int channels = stem_reads_frames(net, geo) ? 3 : net.conv[0].cin_pad;
+  b.padded = a.take_bytes((size_t)kInferChunk * resolution * resolution * channels * es);
   plan_eval(a, net, geo, 0, 5, kInferChunk, b.eb);
 }
 
@@ -1840,7 +1853,7 @@ static hipError_t infer_frames(const Net& net, const Geo& geo, const float* mast
   for (int i0 = 0; i0 < n; i0 += per) {
     const int cnt = std::min(per, n - i0);
     const void* src = reinterpret_cast<const char*>(frames) + i0 * fbytes;
-    const bool raw_ok = stem_pool_ok(net.dt, conv_geom(net, geo, 0, cnt));
+    const bool raw_ok = stem_reads_frames(net, geo);
     if (resolution == H && resolution == W && raw_ok) {
       EKYA_HIP(eval_forward(net, geo, shadow, fold, master, 0, 5, src, cnt, eb, eb.logits,
                             stream));  // the stem reads the frames

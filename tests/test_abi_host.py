@@ -135,3 +135,30 @@ def test_classifier_only_workspace_holds_each_feature_row_once(classes, hidden):
     p = lambda n: binding.ekya_profile_workspace(classes, cfg, n, 64, 64, 40, hidden=hidden)
     for f in (r, p):
         assert abs((f(n1) - f(n0)) / (n1 - n0) - row) < 1.0  # (alignment: 256 bytes a buffer)
+
+
+def test_workspace_has_no_padded_frames_where_the_stem_reads_frames():
+    """bf16 frames up to 224 px wide are read by the eval-mode stem as they
+    are; wider ones need 512 frames (held-out evaluation of a full-depth job:
+    its chunk, here 400) padded to 8 channels.  Inference holds resized
+    3-channel frames instead."""
+    from paper_2012_10557_amd import binding
+    frame = lambda px, channels: px * px * channels * 2
+    r = lambda k, px: binding.ekya_retrain_workspace(6, k, 40, px, px, 400, 1.0, 1, 0.01, 0.9, 1)
+    assert r(2, 226) - r(2, 224) >= 512 * frame(226, 8)
+    assert r(6, 226) - r(6, 224) >= 400 * frame(226, 8)
+    c = [{"k": 2, "subsample_frac": 0.5, "epochs": 1, "batch": 1}]
+    p = lambda px: binding.ekya_profile_workspace(6, c, 40, px, px, 400)
+    assert p(226) - p(224) >= 512 * frame(226, 8)
+    i = lambda px: binding.ekya_infer_workspace(6, px)
+    assert i(226) - i(224) >= 512 * (frame(226, 8) - frame(224, 3))
+
+
+def test_fp32_inference_workspace_has_no_split_scratch():
+    """Every fp32 convolution of an inference call runs unsplit: beyond what
+    grows with the frame area its workspace holds the weights and their two
+    convolution layouts."""
+    from paper_2012_10557_amd import binding
+    i = lambda px: binding.ekya_infer_workspace(6, px, binding.EKYA_FP32)
+    constant = i(64) - (i(128) - i(64)) / 3
+    assert constant <= 3 * binding.ekya_weights_count(6) * 4 + (2 << 20)
