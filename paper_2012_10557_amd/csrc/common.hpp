@@ -86,6 +86,24 @@ __device__ __forceinline__ void mma_unit(f32x4& acc, uint4 a, uint4 b, float*) {
   acc = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(a.w), __uint_as_float(b.w), acc, 0, 0, 0);
 }
 
+typedef __attribute__((address_space(3))) void lds_void;
+
+// 16 bytes per lane from global memory to LDS base + 16 * lane.  Inline asm:
+// the compiler would otherwise make every later LDS read wait for all
+// outstanding loads; completion is tracked with explicit vmcnt waits.
+__device__ __forceinline__ void dma16(const void* src, uint4* lds_dst) {
+  const uint32_t m0 = (uint32_t)(uintptr_t)(lds_void*)lds_dst;
+  asm volatile("global_load_lds_dwordx4 %0, off" ::"v"(src), "{m0}"(m0) : "memory");
+}
+// Waits until at most N vector loads are outstanding (no other counter).  The
+// compiler may still move LDS reads above it: a barrier, or an empty asm with a
+// memory clobber, follows.
+template <int N> __device__ __forceinline__ void wait_vmcnt() {
+  static_assert(N >= 0 && N < 64, "vmcnt range");
+  // gfx9 encoding: vmcnt[3:0], expcnt[6:4], lgkmcnt[11:8], vmcnt[5:4] at [15:14]
+  __builtin_amdgcn_s_waitcnt((N & 15) | ((N >> 4) << 14) | (7 << 4) | (15 << 8));
+}
+
 // acc[i][j] += A_i B_j over one unit of each operand.  For fp32 the four MFMA
 // steps of a unit are the outer loop, so that consecutive MFMAs are
 // independent; each tile's steps keep their order.

@@ -567,16 +567,7 @@ __global__ void wgrad_reduce_kernel(const float* part, int splits, int K, int RS
 // (8 lanes read one 128-byte line) and the MFMA fragment reads (lane = 16-row
 // index + 16 * k-unit) hit distinct banks.  Lanes whose row or tap lies
 // outside the operand read a zero unit instead.
-typedef __attribute__((address_space(3))) void lds_void;
-
 __device__ __align__(16) uint4 g_zero_unit[1];
-
-__device__ __forceinline__ void dma16(const void* src, uint4* lds_dst) {
-  const uint32_t m0 = (uint32_t)(uintptr_t)(lds_void*)lds_dst;
-  // inline asm: the compiler would otherwise make every later LDS read wait
-  // for all outstanding loads; completion is tracked with explicit vmcnt waits
-  asm volatile("global_load_lds_dwordx4 %0, off" ::"v"(src), "{m0}"(m0) : "memory");
-}
 
 // Barrier without __syncthreads' fence (which would wait for every
 // outstanding global load); the vmcnt wait before it orders the LDS writes.
@@ -589,12 +580,6 @@ __device__ __forceinline__ void stage_barrier() {
   asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
   __builtin_amdgcn_s_barrier();
   asm volatile("" ::: "memory");
-}
-
-template <int N> __device__ __forceinline__ void wait_vmcnt() {
-  static_assert(N >= 0 && N < 64, "vmcnt range");
-  // gfx9 encoding: vmcnt[3:0], expcnt[6:4], lgkmcnt[11:8], vmcnt[5:4] at [15:14]
-  __builtin_amdgcn_s_waitcnt((N & 15) | ((N >> 4) << 14) | (7 << 4) | (15 << 8));
 }
 
 // Workgroups are dispatched round-robin over the 8 XCDs (each with its own

@@ -29,20 +29,10 @@
 namespace ekya {
 namespace {
 
-typedef __attribute__((address_space(3))) void lds_void;
-
 __device__ __align__(16) uint4 g_few_zero[1];
 
-// 16 bytes per lane from global memory to LDS base + 16 * lane; completion is
-// tracked by explicit vmcnt waits (inline asm, so that the compiler does not
-// make every later LDS read wait for all copies).
-__device__ __forceinline__ void few_copy(const void* src, uint4* lds_dst) {
-  const uint32_t m0 = (uint32_t)(uintptr_t)(lds_void*)lds_dst;
-  asm volatile("global_load_lds_dwordx4 %0, off" ::"v"(src), "{m0}"(m0) : "memory");
-}
 template <int N> __device__ __forceinline__ void few_wait() {
-  static_assert(N >= 0 && N < 64, "vmcnt range");
-  __builtin_amdgcn_s_waitcnt((N & 15) | ((N >> 4) << 14) | (7 << 4) | (15 << 8));
+  wait_vmcnt<N>();
   asm volatile("" ::: "memory");
 }
 
@@ -143,11 +133,11 @@ __global__ __launch_bounds__(NW * 64) void conv_few_kernel(FewArgs a) {
   auto issue = [&](int st, uint4* slot) {
     const int k0 = st * SE, tap = (tr * g.W + ts) * g.C + tc;
 #pragma unroll
-    for (int i = 0; i < CA; ++i) few_copy(pa[i] + k0, slot + i * 64);
+    for (int i = 0; i < CA; ++i) dma16(pa[i] + k0, slot + i * 64);
 #pragma unroll
     for (int j = 0; j < CB; ++j) {
       const bool in = (unsigned)(h0[j] + tr) < (unsigned)g.H && (unsigned)(w0[j] + ts) < (unsigned)g.W;
-      few_copy(in ? (const void*)(pb[j] + (row[j] + tap)) : zero, slot + (CA + j) * 64);
+      dma16(in ? (const void*)(pb[j] + (row[j] + tap)) : zero, slot + (CA + j) * 64);
     }
     tc += SE;
     if (tc >= g.C) {
@@ -247,11 +237,11 @@ __global__ __launch_bounds__(NG * (TM / 32) * (TN / 32) * 64) void conv_few_shar
   auto issue = [&](int st, uint4* slot) {
     const int k0 = st * SE, tap = (tr * g.W + ts) * g.C + tc;
 #pragma unroll
-    for (int i = 0; i < CA; ++i) few_copy(pa[i] + k0, slot + (wl + WG * i) * 64);
+    for (int i = 0; i < CA; ++i) dma16(pa[i] + k0, slot + (wl + WG * i) * 64);
 #pragma unroll
     for (int j = 0; j < CB; ++j) {
       const bool in = (unsigned)(h0[j] + tr) < (unsigned)g.H && (unsigned)(w0[j] + ts) < (unsigned)g.W;
-      few_copy(in ? (const void*)(pb[j] + (row[j] + tap)) : zero, slot + (TM / 8 + wl + WG * j) * 64);
+      dma16(in ? (const void*)(pb[j] + (row[j] + tap)) : zero, slot + (TM / 8 + wl + WG * j) * 64);
     }
     tc += SE;
     if (tc >= g.C) {

@@ -112,12 +112,10 @@ std::vector<long long> Net::fold_table(int lo, int hi) const {
   return t;
 }
 
-std::vector<long long> Net::pack_table(int lo, int hi, bool with_crsk) const {
+std::vector<long long> Net::pack_table() const {
   std::vector<long long> t;
   for (const ConvL& c : conv)
-    if (c.stage >= lo && c.stage <= hi)
-      t.insert(t.end(), {c.off, c.cout, c.R, c.S, c.cin, c.cin_pad, c.sh_krsc,
-                         with_crsk ? c.sh_crsk : -1LL});
+    t.insert(t.end(), {c.off, c.cout, c.R, c.S, c.cin, c.cin_pad, c.sh_krsc, -1LL});
   return t;
 }
 

@@ -61,7 +61,7 @@ struct Net {
   // Host tables for the kernels (see kernels.hpp for row formats).
   std::vector<long long> layout_table() const;  // every tensor, in order of offset
   std::vector<long long> fold_table(int lo_stage, int hi_stage) const;  // BNs of stages
-  std::vector<long long> pack_table(int lo_stage, int hi_stage, bool with_crsk) const;
+  std::vector<long long> pack_table() const;  // every conv, [K][R][S][C] copies only
 };
 
 // Spatial sizes for one input resolution.

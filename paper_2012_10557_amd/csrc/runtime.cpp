@@ -131,7 +131,7 @@ static hipError_t upload_tables(const Net& net, Tables& t) {
   const long long* layout_at = nullptr;
   put(layout, &layout_at, &t.layout.n, kLayoutCols);
   put(net.fold_table(0, 5), &t.fold_all, &t.n_fold_all, 6);
-  put(net.pack_table(0, 4, false), &t.pack_all, &t.n_pack_all, 8);
+  put(net.pack_table(), &t.pack_all, &t.n_pack_all, 8);
   for (int lo = 0; lo <= 5; ++lo) {
     put(net.fold_table(lo, 5), &t.fold_train[lo], &t.n_fold_train[lo], 6);
     put(sgd_rest_table(net, lo, &t.sgd_rest_max[lo]), &t.sgd_rest[lo], &t.n_sgd_rest[lo], 2);
