@@ -2888,6 +2888,21 @@ bool f32_dma_ok(int rows, long long cols, int red_channels, long long image_elem
   return red_channels % 32 == 0 && image_elems < (1LL << 31) &&
          cdiv(rows, 64) * cdivl(cols, 64) > 448;
 }
+// Of the forward pass, those where the register-staged 128 x 128 tiles are not
+// ahead.  These run at 124 TFLOP/s (64 x 64 copied tiles 115) where their rounds
+// of two blocks per CU are full: 3 x 3, 256 channels, 512 tiles 318 against 341
+// us, 1000 (0.98 of two rounds) 631 and 678, 2020 1256 and 1336; but 740 624 and
+// 503, 900 (0.88) 629 and 623.  From eight rounds on blocks have drifted apart
+// and the last round matters less, from 128 channels: 4100 tiles (0.89) 2646 and
+// 2695, of 128 channels 1340 and 1343, of 64 712 and 691.  Short reductions are
+// bound by their epilogue (1 x 1, 512 channels: 512 tiles 81.3 and 80.4).
+bool f32_fwd_dma_ok(const ConvGeom& g) {
+  const long long cols = (long long)g.N * g.P * g.Q, red = (long long)g.R * g.S * g.C;
+  const long long t = g.K / 128 * cdivl(cols, 128), rounds = cdivl(t, kTargetBlocks);
+  const bool full = 20 * t >= 19 * kTargetBlocks * rounds ? red > 512 : rounds >= 8 && red >= 1152;
+  if (g.K % 128 == 0 && t >= kTargetBlocks && full) return false;
+  return f32_dma_ok(g.K, cols, g.C, (long long)g.H * g.W * g.C);
+}
 // Below kTargetBlocks tiles, where the register-staged tiles would split the
 // reduction, its sums are kept in runs (RunSum): one chain of 2304 products
 // rounds to 5.9e-7 against float64, its split in three to 3.5e-7, runs to
@@ -3116,8 +3131,7 @@ hipError_t conv_fwd_t(const ConvGeom& g, const void* x, const void* w, void* y,
   }
   const bool direct = sizeof(T) == 4 && lds_copy_ok(x);
   if (direct && conv_few_ok(DT_F32, g)) return conv_few_fwd(DT_F32, g, x, w, y, epi, stream);
-  if (direct &&
-      f32_dma_ok(g.K, (long long)g.N * g.P * g.Q, g.C, (long long)g.H * g.W * g.C)) {
+  if (direct && f32_fwd_dma_ok(g)) {
     DmaFwdArgsT<float> a{g, (const float*)x, (const float*)w, (float*)y, epi,
                          SplitOut{nullptr, 1, g.R * g.S * g.C / 32}, 0, 0};
     const long long cols = (long long)g.N * g.P * g.Q;
@@ -3210,7 +3224,7 @@ size_t conv_split_workspace_floats(int dt, const ConvGeom& g, bool dgrad, bool g
   if (!general && !dgrad && conv_few_ok(dt, g)) return 0;
   if (!general && dt == DT_F32 &&
       (dgrad ? f32_dma_ok(g.C, (long long)g.N * g.H * g.W, g.K, (long long)g.P * g.Q * g.K)
-             : f32_dma_ok(g.K, (long long)g.N * g.P * g.Q, g.C, (long long)g.H * g.W * g.C)))
+             : f32_fwd_dma_ok(g)))
     return 0;
   if (dt == DT_BF16 && dgrad) {
     const long long npix = (long long)g.N * g.H * g.W;

@@ -2,7 +2,8 @@
 gradient: tile remainders in channels and pixels, stride 2 with odd and even
 sizes, 1 x 1 and 5 x 5 filters, 32 and 96 reduced channels; and 1 x 1 filters
 of too few channels for the few-pixel kernel beyond 128 tiles, up to 448, on
-the register-staged tiles.  Reference: the same sums in float64.  An output sums n products in float32, so it may be off
+the register-staged tiles, as do 3 x 3 filters whose 128 x 128 tiles fill
+rounds of two per CU.  Reference: the same sums in float64.  An output sums n products in float32, so it may be off
 by n 2^-24 sum |x w|."""
 import pytest
 
@@ -13,9 +14,11 @@ SHAPES = [(19, 40, 40, 64, 64, 3, 1), (5, 57, 55, 96, 160, 3, 2), (9, 41, 40, 32
           (13, 26, 30, 160, 224, 1, 1), (33, 29, 31, 64, 96, 1, 2), (60, 7, 9, 128, 512, 3, 1)]
 # 1 x 1: 314, 288 and 130 tiles forward
 SHORT = [(25, 20, 20, 64, 128, 1, 1), (36, 31, 32, 128, 128, 1, 2), (3, 52, 53, 32, 64, 1, 1)]
+# 512 tiles of 128 x 128, and 983 of 1024 (the last one partly filled)
+FULL = [(16, 64, 64, 64, 128, 3, 1), (31, 45, 45, 96, 256, 3, 1)]
 
 
-@pytest.mark.parametrize("N,H,W,C,K,R,stride", SHAPES + SHORT)
+@pytest.mark.parametrize("N,H,W,C,K,R,stride", SHAPES + SHORT + FULL)
 def test_f32_convolution_matches_float64(N, H, W, C, K, R, stride):
     import torch
     import torch.nn.functional as F
