@@ -2881,8 +2881,9 @@ hipError_t dispatch_dma(Args a, const DmaPlan& p, long long cols, int rows, hipS
 // where they do not (layer 4, 296 tiles on 256 CUs); 128 x 128 more so on
 // both sides.  The data gradient with its filter packing: 96 images, 28 x 28 x
 // 128 306 -> 238 us, 14 x 14 x 256 385 -> 276, stride 2 to 28 x 28 x 128 584
-// -> 462.  Below 449 tiles conv_few_fwd takes the forward pass, and the data
-// gradient keeps plan_tiles' split reductions, which fill the chip.
+// -> 462.  Below 449 tiles the data gradient keeps plan_tiles' split reductions,
+// which fill the chip, and the forward pass goes to conv_few_fwd or, where
+// conv_few_ok refuses (short reductions above 128 tiles), to plan_tiles as well.
 // Offsets within an image are 32-bit.
 bool f32_dma_ok(int rows, long long cols, int red_channels, long long image_elems) {
   return red_channels % 32 == 0 && image_elems < (1LL << 31) &&

@@ -347,12 +347,14 @@ bool conv_few_ok(int dt, const ConvGeom& g) {
   const long long npix = (long long)g.N * g.P * g.Q, red = (long long)g.R * g.S * g.C;
   // At most two 64 x 64 tiles per CU: at 512 tiles (256 channels x 8192 pixels)
   // it is a third faster than split or half-filled large tiles, at 784 (12544
-  // pixels) 42.6 against 31.4 us.  fp32, bound by the MFMAs there, gains up to
-  // 400 tiles (93 against 107 us) and loses at 512 (64 channels x 32768 pixels:
-  // 35.0 against 32.8).  With fewer stages than waves (1 x 1 filters) half a
-  // tile per CU: 64 -> 128 channels at 3136 pixels (98 tiles) 5.1 -> 4.4 us, at
-  // 14400 (450) 4.3 -> 6.6.
-  const long long most = red < 8 * se ? 128 : dt == DT_F32 ? 448 : 512;
+  // pixels) 42.6 against 31.4 us.  fp32, bound by the MFMAs there, meets 64 x 64
+  // copied tiles with sums in runs as well: in inference at 224 px (layers 1 to
+  // 4 of 10, 20, 40 and 80 frames, 490 tiles) 569, 928, 1653 and 3110 us per
+  // call here, 559, 925, 1665 and 3150 there, so only long reductions go beyond
+  // 448 tiles; at 512 (8192 pixels x 256) 94.6 against 90.9.  With fewer stages
+  // than waves (1 x 1 filters) half a tile per CU: 64 -> 128 channels at 3136
+  // pixels (98 tiles) 5.1 -> 4.4 us, at 14400 (450) 4.3 -> 6.6.
+  const long long most = red < 8 * se ? 128 : dt == DT_BF16 ? 512 : red < 2048 ? 448 : 511;
   // Offsets within an image are 32-bit.
   return g.N > 0 && g.C % se == 0 && g.K % 4 == 0 && red < (1 << 24) &&
          ((long long)g.H + 2 * g.pad) * g.W * g.C < (1LL << 31) &&
