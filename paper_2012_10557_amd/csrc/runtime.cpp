@@ -331,9 +331,12 @@ hipError_t create_masked_stream(const std::vector<uint32_t>& mask, hipStream_t* 
 
 // --------------------------------------------------------- eval forward
 // Classes up to which pooling and classifier are one launch: a block per frame
-// reads the whole classifier (at 6 classes 5.4 us against 13.4 + 3.9 for four
-// frames; a wide classifier goes to the tiled product).
-static constexpr int kHeadFusedClasses = 16;
+// reads the whole classifier, eight classes at a time, where the tiled product
+// reads it once per 16 frames.  4, 64 and 500 frames at 64 px, together and
+// apart: 6 classes 137.4, 154.6, 448.2 and 137.5, 155.1, 447.8 us per call; 12
+// classes 140.7, 158.6, 453.4 and 136.9, 155.7, 448.5; 17 144.6, 162.2, 458.0
+// and 138.3, 156.1, 448.4.
+static constexpr int kHeadFusedClasses = 8;
 
 // Buffers for running stages in eval mode on up to `cap` frames.
 struct EvalBufs {

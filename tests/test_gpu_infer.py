@@ -2,7 +2,7 @@
 ekya_infer at the workload's resolutions against stored oracle logits: 520
 drifting 224 px frames (two equal 260-frame chunks, so the chunk split runs),
 resized to 224 (the stem reads the frames directly), 160 and 112 (resize
-kernel, then the padded-input stem).  Labels equal the oracle's except where
+kernel, then the stem on the resized frames).  Labels equal the oracle's except where
 its top-2 logit margin is below 2 tol x the frame's logit scale
 max_j sum_i |W_ji f_i| (f the pooled features): a relative error tol in the
 features -- 2e-2 for bf16 activations, 1e-5 for fp32 -- moves each logit by
@@ -71,3 +71,29 @@ def test_infer_labels_match_oracle(ctx, golden, prec, res):
           f"within the tie margin, oracle class counts {counts.tolist()}")
     assert (counts > 0).sum() >= 3, "the stored case must exercise several classes"
     assert np.all((got == ref) | tie), np.nonzero((got != ref) & ~tie)
+
+
+@pytest.mark.parametrize("classes", [1, 8, 9, 16, 17])
+def test_labels_at_the_edges_of_the_fused_head(classes):
+    """Pooling and classifier are one launch for up to 8 classes.  float32: a
+    logit is within 1e-5 of its scale max_j sum_i |W_ji f_i| + |b_j|."""
+    import torch
+    from oracle.resnet18 import ResNet18
+    from paper_2012_10557_amd import binding
+    net = ResNet18(classes)
+    w = kaiming_resnet18_weights(seed=5, n_classes=classes)
+    frames, _ = make_frames(WindowSpec(21, 0, 40, 40, drift="drift", seed=4), 21, 1, 2)
+    P = net.unpack(w)
+    f = net.forward(P, frames.astype(np.float64), 0, 4, train=False, tape={})
+    w[-classes:] = -P["fc.weight"] @ f.mean(0)  # labels of several classes
+    P = net.unpack(w)
+    logits = f @ P["fc.weight"].T + P["fc.bias"]
+    scale = (np.abs(f) @ np.abs(P["fc.weight"]).T + np.abs(P["fc.bias"])).max(1)
+    c = binding.ekya_create(0, classes)
+    try:
+        got = binding.ekya_infer(c, torch.tensor(w, device="cuda"), to_dev(frames, "f32"), 40).cpu().numpy()
+    finally:
+        binding.ekya_destroy(c)
+    best = logits.max(1)
+    assert len(np.unique(got)) > (classes > 1)
+    assert np.all(best - logits[np.arange(21), got] <= 2 * TOL["f32"] * scale)
