@@ -1710,11 +1710,11 @@ ekya_status run_profile(Ctx& c, const float* weights, const ekya_profile_cfg* cf
     for (auto& ci : caches) order.push_back(&ci);
     std::sort(order.begin(), order.end(),
               [](const CacheInfo* a, const CacheInfo* b) { return a->lowest < b->lowest; });
-    const CacheInfo* below = nullptr;
-    for (CacheInfo* c : order) {
-      CacheInfo& ci = *c;
-      const CacheInfo* from = below && below->n_rows_s == ci.n_rows_s ? below : nullptr;
-      below = &ci;
+    for (size_t i = 0; i < order.size(); ++i) {
+      CacheInfo& ci = *order[i];
+      const CacheInfo* from = nullptr;  // the deepest below it with the same rows
+      for (size_t b = 0; b < i; ++b)
+        if (order[b]->n_rows_s == ci.n_rows_s) from = order[b];
       if (from) {
         const long long ft = from->n_rows_s * from->row_bytes, ct = ci.n_rows_s * ci.row_bytes;
         EKYA_HIP(extend_cache(net, geo, pshadow, pfold, pmaster, from->lowest, from->p,
