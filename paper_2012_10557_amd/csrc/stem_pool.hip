@@ -26,10 +26,10 @@
 //  - blocks are persistent, two per CU, one staging while the other computes.
 // One MFMA k-step is one filter row: 8 taps (the 8th zero) x 4 channels, a
 // lane's operand 2 adjacent pixels of the staged row.
-// Measured (MI355X): 500 frames at 224 px 657 -> 263 us (450 TFLOP/s of useful
+// Measured (MI355X): 500 frames at 224 px 656 -> 276 us (430 TFLOP/s of useful
 // products, 1.3 TB/s; before, a wave per stem row finished every stem value
-// and exchanged rows through LDS, one block per CU), 500 at 112 px 206 -> 85,
-// 4 at 224 px 25.6 -> 18.0.
+// and exchanged rows through LDS, one block per CU; without the waves' choice
+// of path 267), 500 at 112 px 200 -> 81, 4 at 224 px 26.0 -> 17.8.
 #include <type_traits>
 
 #include "kernels.hpp"
@@ -329,6 +329,10 @@ hipError_t stem_pool_fwd(int dt, const ConvGeom& g, const void* frames, const in
     e1 = t->take();
     EKYA_HIP(hipEventRecord(e0, stream));
   }
+  // The running maxima are registers, by number of 16-column tiles: exact at the
+  // frame sizes in use (64, 112, 160 and 224 px: 2, 4, 5, 7); widths in between
+  // take the next and compute up to a third more than they store (500 frames at
+  // 96 px, 3 tiles in 4, 144 -> 67 us; at 192 px, 6 in 7, 492 -> 222).
   switch (cdiv(g.Q, 16)) {
     case 1: case 2: launch_stem_pool<2>(a, wide, blocks, stream); break;
     case 3: case 4: launch_stem_pool<4>(a, wide, blocks, stream); break;
