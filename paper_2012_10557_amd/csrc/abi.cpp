@@ -306,12 +306,14 @@ namespace {
 
 // A call's temporaries, in one allocation where that costs nothing.  Below 2 MB
 // HIP carves an allocation from memory it holds already (allocation and release
-// 2 us), from there on it maps memory (24 us and more): where no temporary is
-// that large by itself, they share allocations up to that size only (weight
-// gradient of 64 -> 128 channels, 1 x 1, 133 images of 36 x 36, with 2016 and 32
-// KB: 110 us in one allocation, 78 in two).
+// 2 us), up to 64 MB in all it maps memory (17 to 24 us), beyond that it gives the
+// memory back as well (290 us).  So temporaries share allocations up to the first
+// of these sizes that no single one passes (weight gradients: 64 -> 128 channels,
+// 1 x 1, 133 images of 36 x 36, with 2016 and 32 KB, 110 us in one allocation, 78
+// in two; 96 -> 512 channels, 3 x 3, fp32, 26 of 63 x 69, with 62.4 and 1.7 MB, 1590
+// and 1335).
 struct Tmp {
-  static constexpr size_t kMapped = 2040 << 10;
+  static constexpr size_t kMapped = 2040 << 10, kKept = 64 << 20;
   struct Piece {
     size_t bytes;  // as asked for
     char* p;
@@ -325,9 +327,9 @@ struct Tmp {
   static size_t padded(size_t bytes) { return (bytes + 64 + 255) & ~(size_t)255; }
   // What get() will be asked for, in that order (0: not asked for).
   hipError_t reserve(std::initializer_list<size_t> bytes) {
-    bool mapped = false;
-    for (size_t n : bytes) mapped = mapped || padded(n) > kMapped;
-    size_t size = 0, first = 0;
+    size_t limit = kMapped, size = 0, first = 0;
+    for (size_t n : bytes)
+      if (n && padded(n) > kMapped) limit = kKept;
     auto close = [&]() -> hipError_t {  // one block for the pieces since the last
       char* b = nullptr;
       if (size) EKYA_HIP(hipMalloc((void**)&b, size));
@@ -341,7 +343,7 @@ struct Tmp {
     };
     for (size_t n : bytes) {
       if (!n) continue;
-      if (!mapped && size + padded(n) > kMapped) EKYA_HIP(close());
+      if (size + padded(n) > limit) EKYA_HIP(close());
       pieces.push_back({n, nullptr});
       size += padded(n);
     }
