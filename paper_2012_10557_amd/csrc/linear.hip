@@ -175,6 +175,36 @@ __global__ __launch_bounds__(256) void linear_kernel(LinArgs a) {
   }
 }
 
+// At most JN outputs per row: a block takes a row, a strided slice per thread
+// and then the wave and block reductions in one order.
+template <int JN>
+__global__ __launch_bounds__(256) void linear_rows_kernel(LinArgs a) {
+  __shared__ float red[4][JN];
+  const int m = blockIdx.x, t = threadIdx.x;
+  const float* row = a.A + (a.rows ? a.rows[m] : m) * a.lda;
+  float s[JN];
+#pragma unroll
+  for (int j = 0; j < JN; ++j) s[j] = 0.f;
+  for (int k = t; k < a.K; k += 256) {
+    const float x = row[k];
+#pragma unroll
+    for (int j = 0; j < JN; ++j)
+      if (j < a.N) s[j] += x * a.B[j * a.ldb + k];
+  }
+#pragma unroll
+  for (int j = 0; j < JN; ++j) {
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) s[j] += __shfl_xor(s[j], o, 64);
+    if ((t & 63) == 0) red[t >> 6][j] = s[j];
+  }
+  __syncthreads();
+  if (t < a.N) {
+    float v = (red[0][t] + red[1][t]) + (red[2][t] + red[3][t]);
+    if (a.bias) v += a.bias[t];
+    a.C[(long long)m * a.N + t] = a.relu ? fmaxf(v, 0.f) : v;
+  }
+}
+
 int lin_vec(const float* p, long long ld, int K) {
   return reinterpret_cast<uintptr_t>(p) % 16 == 0 && ld % 4 == 0 && K % 4 == 0;
 }
@@ -222,6 +252,21 @@ hipError_t fc_fwd(const float* f, const float* W, const float* b, int N, int I, 
   a.relu = relu;
   a.rows = rows;
   a.C = z;
+  // Few outputs leave most of a tile's columns unused; its waves make up for it
+  // with 16-byte loads, or with many short rows to share the weights.  Without
+  // either, and for one output, a block per row (synchronous calls, tiles and
+  // rows: 39 rows of 1486 -> 2 30.8 and 22.4 us, 400 of 513 -> 6 25.3 and 22.5, 10 of
+  // 4097 -> 8 53.1 and 34.3, 3000 of 2050 -> 3 46.1 and 31.4, but 3000 of 1486 -> 8
+  // 32.7 and 37.2, 4096 of 513 -> 6 25.4 and 29.9; 39 of 1486 -> 1 29.6 and 20.2)
+  const bool vec = lin_vec(f, I, I) && lin_vec(W, I, I);
+  if (J == 1 || (J > 1 && J <= 8 && !vec && (N <= 1024 || I >= 2048))) {
+    if (I < 1) return hipErrorInvalidValue;
+    if (J == 1)
+      hipLaunchKernelGGL(linear_rows_kernel<1>, dim3(N), dim3(256), 0, stream, a);
+    else
+      hipLaunchKernelGGL(linear_rows_kernel<8>, dim3(N), dim3(256), 0, stream, a);
+    return hipGetLastError();
+  }
   return linear<true, true>(a, stream);
 }
 

@@ -1,16 +1,18 @@
 """Fully connected layers at the sizes where the tiled kernel changes: tile
 edges and remainders (16 and 32 wide), reductions shorter than one MFMA step,
 not a multiple of 16 or of the chunks in flight, operands not 16-byte aligned,
-both tile sizes, and reductions of up to 64 elements in both (one chunk in
-flight).  Reference: the same products in float64.  An output is
-sum_k a_k b_k in float32 in some order, so it may be off by K 2^-24 sum |a b|."""
+both tile sizes, reductions of up to 64 elements in both (one chunk in flight),
+and the edges of the block per row that few outputs without 16-byte loads take.
+Reference: the same products in float64.  An output is sum_k a_k b_k in float32 in
+some order, so it may be off by K 2^-24 sum |a b|."""
 import pytest
 
 pytestmark = pytest.mark.gpu
 
 SIZES = [(1, 1, 1), (3, 5, 2), (16, 16, 16), (17, 33, 15), (64, 512, 6), (37, 501, 77), (31, 512, 129),
          (128, 516, 500), (400, 1024, 6), (513, 512, 1000), (5, 4096, 6), (1100, 40, 300),
-         (33, 512, 520), (64, 520, 600), (65, 520, 600)]
+         (33, 512, 520), (64, 520, 600), (65, 520, 600),
+         (1024, 77, 8), (1025, 77, 8), (1025, 2049, 3), (40, 301, 9), (300, 512, 1)]
 
 
 def _close(got, ref, a, b, K):
