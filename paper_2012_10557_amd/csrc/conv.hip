@@ -3251,6 +3251,23 @@ size_t conv_split_workspace_floats(int dt, const ConvGeom& g, bool dgrad, bool g
   return p.splits > 1 ? (size_t)p.splits * npix * g.K : 0;
 }
 
+size_t conv_eval_workspace_floats(int dt, ConvGeom g, int most) {
+  // conv_few_ok holds up to some number of images: the last one by bisection
+  // (asked for each of 512 it would cost a call's first planning 50 us)
+  int few = 0, hi = most;
+  while (few < hi) {
+    g.N = few + (hi - few + 1) / 2;
+    if (conv_few_ok(dt, g)) few = g.N; else hi = g.N - 1;
+  }
+  size_t m = 0;
+  for (g.N = few + 1; g.N <= most; ++g.N) {
+    // plan_tiles does not split from here on
+    if (dt == DT_F32 && cdiv(g.K, 64) * cdivl((long long)g.N * g.P * g.Q, 64) >= kTargetBlocks) break;
+    m = std::max(m, conv_split_workspace_floats(dt, g, false, dt == DT_BF16));
+  }
+  return m;
+}
+
 namespace {
 // Direct-to-LDS weight-gradient plan: 64 x 128 tiles (64 x 64 when K is not a
 // multiple of 128), the pixel reduction split until ~576 blocks, keeping

@@ -119,6 +119,8 @@ hipError_t conv_dgrad(int dt, const ConvGeom& g, const void* dy, const void* w_c
 // general: also for calls that the one-launch kernels do not take (a BatchNorm
 // sink, fp32 activations that do not start on 16 bytes).
 size_t conv_split_workspace_floats(int dt, const ConvGeom& g, bool dgrad, bool general);
+// The most that forward convolutions of 1 to `most` images ask for (not general).
+size_t conv_eval_workspace_floats(int dt, ConvGeom g, int most);
 // Whether fp32 activations at p may go to LDS by 16-byte copies.
 bool lds_copy_ok(const void* p);
 // The bf16 data gradient of a 3x3 / stride-2 / pad-1 convolution g plus that

@@ -387,9 +387,7 @@ static void plan_eval(Arena& a, const Net& net, const Geo& g, int lo, int hi, in
     size_t ws = 16;
     for (size_t i = 0; i < net.conv.size(); ++i)
       if (net.conv[i].stage >= lo && net.conv[i].stage <= hi)
-        for (int n = 1; n <= cap; ++n)
-          ws = std::max(ws, conv_split_workspace_floats(net.dt, conv_geom(net, g, (int)i, n), false,
-                                                        false));
+        ws = std::max(ws, conv_eval_workspace_floats(net.dt, conv_geom(net, g, (int)i, 1), cap));
     return ws;
   });
   b.ws = a.take<float>(b.ws_floats);
