@@ -257,14 +257,19 @@ hipError_t fc_fwd(const float* f, const float* W, const float* b, int N, int I, 
   // either, and for one output, a block per row (synchronous calls, tiles and
   // rows: 39 rows of 1486 -> 2 30.8 and 22.4 us, 400 of 513 -> 6 25.3 and 22.5, 10 of
   // 4097 -> 8 53.1 and 34.3, 3000 of 2050 -> 3 46.1 and 31.4, but 3000 of 1486 -> 8
-  // 32.7 and 37.2, 4096 of 513 -> 6 25.4 and 29.9; 39 of 1486 -> 1 29.6 and 20.2)
+  // 32.7 and 37.2, 4096 of 513 -> 6 25.4 and 29.9; 39 of 1486 -> 1 29.6 and 20.2; up to
+  // 16 outputs long rows only: 93 of 1503 -> 11 33.9 and 29.6, 1000 of 513 -> 16 25.2
+  // and 27.8, 3000 of 2049 -> 16 45.6 and 59.7)
   const bool vec = lin_vec(f, I, I) && lin_vec(W, I, I);
-  if (J == 1 || (J > 1 && J <= 8 && !vec && (N <= 1024 || I >= 2048))) {
+  const bool few = J <= 8 ? N <= 1024 || I >= 2048 : J <= 16 && N <= 1024 && I >= 1024;
+  if (J == 1 || (J > 1 && !vec && few)) {
     if (I < 1) return hipErrorInvalidValue;
     if (J == 1)
       hipLaunchKernelGGL(linear_rows_kernel<1>, dim3(N), dim3(256), 0, stream, a);
-    else
+    else if (J <= 8)
       hipLaunchKernelGGL(linear_rows_kernel<8>, dim3(N), dim3(256), 0, stream, a);
+    else
+      hipLaunchKernelGGL(linear_rows_kernel<16>, dim3(N), dim3(256), 0, stream, a);
     return hipGetLastError();
   }
   return linear<true, true>(a, stream);

@@ -12,7 +12,8 @@ pytestmark = pytest.mark.gpu
 SIZES = [(1, 1, 1), (3, 5, 2), (16, 16, 16), (17, 33, 15), (64, 512, 6), (37, 501, 77), (31, 512, 129),
          (128, 516, 500), (400, 1024, 6), (513, 512, 1000), (5, 4096, 6), (1100, 40, 300),
          (33, 512, 520), (64, 520, 600), (65, 520, 600),
-         (1024, 77, 8), (1025, 77, 8), (1025, 2049, 3), (40, 301, 9), (300, 512, 1)]
+         (1024, 77, 8), (1025, 77, 8), (1025, 2049, 3), (40, 301, 9), (300, 512, 1),
+         (90, 1025, 16), (1025, 1025, 9)]
 
 
 def _close(got, ref, a, b, K):
