@@ -262,7 +262,8 @@ hipError_t fc_fwd(const float* f, const float* W, const float* b, int N, int I, 
   // and 27.8, 3000 of 2049 -> 16 45.6 and 59.7)
   const bool vec = lin_vec(f, I, I) && lin_vec(W, I, I);
   const bool few = J <= 8 ? N <= 1024 || I >= 2048 : J <= 16 && N <= 1024 && I >= 1024;
-  if (J == 1 || (J > 1 && !vec && few)) {
+  // (a launch has fewer than 2^32 threads)
+  if (N < (1 << 24) && (J == 1 || (J > 1 && !vec && few))) {
     if (I < 1) return hipErrorInvalidValue;
     if (J == 1)
       hipLaunchKernelGGL(linear_rows_kernel<1>, dim3(N), dim3(256), 0, stream, a);

@@ -40,3 +40,15 @@ def test_linear_matches_float64(N, I, J, offset):
     _close(df, dz.double() @ W.double(), dz, W, J)
     _close(dW, dz.double().t() @ f.double(), dz.t(), f, N)
     _close(db[:, None], dz.double().sum(0)[:, None], dz.t(), ones, N)
+
+
+@pytest.mark.parametrize("N", [(1 << 24) - 1, 1 << 24])
+def test_one_output_of_more_rows_than_a_launch_has_blocks(N):
+    import torch
+    from paper_2012_10557_amd import binding
+    gen = torch.Generator(device="cuda").manual_seed(1)
+    f, W, b = (torch.randn(*s, generator=gen, device="cuda") for s in ((N, 3), (1, 3), (1,)))
+    z = binding.ekya_op_linear(f, W, b)
+    ref = f.double() @ W.double().t() + b.double()
+    mag = f.double().abs() @ W.double().abs().t() + b.double().abs()
+    assert ((z.double() - ref).abs() <= 4 * 2.0 ** -24 * mag).all()
